@@ -42,7 +42,8 @@ def log(msg):
 
 KERNEL_SOURCES = {1: ("attn_mfma.hip", "attn_mfma_common.h", "kvshot_common.h"),
                   3: ("attn_tall.hip", "attn_mfma_common.h", "kvshot_common.h")}
-KERNEL_NAMES = {1: "attn_mfma_kernel", 2: "attn_generic_kernel", 3: "attn_tall_kernel"}
+KERNEL_NAMES = {1: "attn_mfma_kernel", 2: "attn_generic_kernel", 3: "attn_tall_kernel",
+                4: "attn_fp32_kernel"}
 PROFILE_PREFIX = {1: "attn_mfma", 3: "attn_tall"}
 
 
@@ -438,7 +439,7 @@ def main():
                    "batch": B, "ctx_len_max": T_max, "draft_queries": n, "mode": args.mode if d["mode"] == "step"
                    else "tree", "page_size": P, "splits": plan["splits"], "workgroups": plan["workgroups"],
                    "cold_caches": bool(args.cold), "launch": "python" if args.no_graph else "hip graph replay",
-                   "path": {1: "mfma", 2: "generic", 3: "mfma (tall tiles)"}[plan["path"]],
+                   "path": {1: "mfma", 2: "generic", 3: "mfma (tall tiles)", 4: "float32 mfma"}[plan["path"]],
                    "page_table": "contiguous" if args.contiguous else "random permutation"},
         "call_ms": call_ms,
         "roofline": {"bound": "hbm", "achieved": round(achieved, 2), "peak": PEAK_HBM_GBS, "unit": "GB/s",

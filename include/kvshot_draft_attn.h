@@ -216,12 +216,13 @@ typedef enum {
   KVSHOT_OPT_SPLITS = 0,   /* value 0: automatic split-K count; n > 0: use n (clamped to the workspace) */
   KVSHOT_OPT_PATH = 1,     /* 0 automatic, 1 MFMA kernels (bf16 only; 256-row query tiles take the
                               tall-tile kernel), 2 generic VALU kernel, 3 the general MFMA kernel for
-                              every tile height (bf16 only) */
+                              every tile height (bf16 only).  Automatic: bf16 takes the MFMA kernels,
+                              float32 the kernel on float32 matrix instructions. */
   KVSHOT_OPT_PROFILE = 2   /* 1: record HIP events around the attention and combine kernels of every call */
 } kvshot_option;
 kvshot_status kvshot_draft_attn_set_option(kvshot_handle h, int32_t option, int64_t value);
 
-/* Plan a call would use: split count, path (1 MFMA, 2 generic), 32-row query tiles,
+/* Plan a call would use: split count, path (1 MFMA, 2 generic, 3 tall tiles, 4 float32 MFMA), 32-row query tiles,
  * and grid size in workgroups of the attention kernel.  Host outputs, each nullable. */
 kvshot_status kvshot_draft_attn_plan(kvshot_handle h, int32_t batch, int32_t n_queries, int32_t max_ctx_len_hint,
                                      int32_t* splits, int32_t* path, int32_t* row_tiles, int32_t* workgroups);

@@ -62,7 +62,7 @@ bool is_pow2(int v) { return v > 0 && (v & (v - 1)) == 0; }
 bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 
 struct Plan {
-  int path;        // 1 mfma, 2 generic
+  int path;        // 1 mfma, 2 generic (vector ALU), 3 tall tiles, 4 float32 mfma
   int row_tiles;   // 32-row query tiles per (sequence, KV head)
   int kernel_row_tiles;  // of which one workgroup holds (row_groups = row_tiles / kernel_row_tiles)
   int row_groups;
@@ -104,6 +104,11 @@ Plan make_plan(const kvshot_ctx* c, int batch, int nq, int max_ctx, bool allow_t
     pl.row_groups = 1;
     pl.waves_per_wg = 4;
     pl.key_streams = 1;
+    if (c->opt_path != 2) {
+      // float32 inputs: workgroups of one or two 16-row tiles
+      pl.path = 4;
+      pl.row_groups = (pl.rows + fp32_rows_per_wg(pl.rows) - 1) / fp32_rows_per_wg(pl.rows);
+    }
   } else if (pl.row_tiles >= kTallRowTiles && allow_tall && c->opt_path != 3 && use_tall_kernel()) {
     // 256-row tiles (draft trees, 33..64 queries at G = 4): the tall-tile kernel
     pl.path = 3;
@@ -128,10 +133,14 @@ Plan make_plan(const kvshot_ctx* c, int batch, int nq, int max_ctx, bool allow_t
     // blocks per wave.  (Each workgroup starts with a dependent chain of
     // loads -- length, page ids, K/V, RoPE table -- that only other resident
     // workgroups can hide, so more, shorter workgroups lose.)
-    const int per_cu = generic ? 2 : (pl.path == 3 ? 1 : mfma_wgs_per_cu(pl.kernel_row_tiles));
+    const int per_cu = pl.path == 2 ? 2 : (pl.path == 3 || pl.path == 4 ? 1 : mfma_wgs_per_cu(pl.kernel_row_tiles));
     const int target_wgs = c->num_cus * per_cu;
     splits = (target_wgs + pairs - 1) / pairs;
-    const int cap = nb / (pl.key_streams * 4);
+    // float32: 16 keys and 16 rows take a wave about 1 us of matrix instructions, so one key block
+    // (two waves' work) per workgroup still gains: 512 keys, 16 rows take 21.8 us unsplit and 13.4 us
+    // in 16 splits, 4096 keys 37.7 us in 4 and 19.0 us in 32.  From 256 keys down the second launch
+    // costs a caller what the splits gain (15.9 us against 12.6 us + 3 us).
+    const int cap = pl.path == 4 ? (nb > 8 ? nb : 1) : nb / (pl.key_streams * 4);
     splits = splits > cap ? cap : splits;
   }
   if (splits < 1) splits = 1;
@@ -305,6 +314,7 @@ kvshot_status run_call(kvshot_ctx* c, const kvshot_call& a, void* stream, const 
   }
   hipError_t e = pl.path == 1   ? launch_attn_mfma(p, pl.kernel_row_tiles, s)
                  : pl.path == 3 ? launch_attn_tall(p, s)
+                 : pl.path == 4 ? launch_attn_fp32(p, s)
                                 : launch_attn_generic(p, g.dtype == KVSHOT_BF16, s);
   if (e != hipSuccess) return KVSHOT_ERR_DEVICE;
   if (slot && hipEventRecord(slot->ev[1], s) != hipSuccess) return KVSHOT_ERR_DEVICE;

@@ -1,6 +1,6 @@
-// Generic draft attention on the vector ALU, for float32 inputs (and as a
-// second bf16 path behind an option).  Same split-K plan, partial layout and
-// index code as the MFMA kernel; arithmetic entirely in float32.
+// Generic draft attention on the vector ALU: a second path for both input types
+// behind an option (path 2).  Same partial layout and index code as the MFMA
+// kernels; arithmetic entirely in float32.
 //
 // A 256-thread workgroup serves one (split, KV head, sequence).  Thread t owns
 // query row (t / 16) of a 16-row tile and the 8 channels 8 * (t % 16) .. +7.

@@ -252,6 +252,8 @@ hipError_t launch_attn_mfma(const AttnParams& p, int kernel_row_tiles, hipStream
 hipError_t launch_attn_tall(const AttnParams& p, hipStream_t s);
 int tall_waves_per_wg();
 int tall_max_blocks();
+int fp32_rows_per_wg(int rows);
+hipError_t launch_attn_fp32(const AttnParams& p, hipStream_t s);
 hipError_t launch_attn_generic(const AttnParams& p, int bf16_in, hipStream_t s);
 hipError_t launch_combine(const CombineParams& p, hipStream_t s);
 hipError_t launch_gather_kv(const AttnParams& p, int max_ctx, void* k_dense, void* v_dense, int bf16, hipStream_t s);

@@ -115,6 +115,12 @@ hipError_t launch_attn_tall(const AttnParams& p, hipStream_t) {
   check_attn(p);
   return hipSuccess;
 }
+int fp32_rows_per_wg(int rows) { return rows <= 16 ? 16 : 32; }
+hipError_t launch_attn_fp32(const AttnParams& p, hipStream_t) {
+  need(p.row_groups * fp32_rows_per_wg(p.rows) >= p.rows, "float32 row groups");
+  check_attn(p);
+  return hipSuccess;
+}
 hipError_t launch_attn_generic(const AttnParams& p, int, hipStream_t) {
   check_attn(p);
   return hipSuccess;
