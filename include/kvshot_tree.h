@@ -102,6 +102,27 @@ kvshot_status kvshot_tree_select(int32_t batch, int32_t depth, int32_t k, int32_
                                  const int32_t* level_tokens, const float* level_scores, int32_t* parents,
                                  int32_t* tokens, int32_t* depths, float* scores, void* stream);
 
+/* Bytes of workspace kvshot_tree_grow needs: 136 per row and chunk (none for rows
+ * of one chunk) and 8 k per row, for batch (1 + (depth - 1) k) rows.  -1 for sizes
+ * kvshot_tree_grow does not take. */
+int64_t kvshot_tree_grow_workspace_bytes(int32_t batch, int32_t depth, int32_t k, int32_t vocab);
+
+/* A whole growth over logits that are all there: the same result, bit for bit, as
+ * kvshot_tree_level for each level followed by kvshot_tree_select, in three
+ * launches (the top-k of every level's rows does not wait for the levels before).
+ * level_logits (host) array of `depth` device pointers: level 0 [batch][1][vocab],
+ *           the others [batch][k][vocab], frontier nodes in the order the previous
+ *           level returns them; rows contiguous
+ * parents, tokens, depths int32 [batch][n], scores float32 [batch][n]: the tree
+ * workspace device scratch of workspace_bytes >= kvshot_tree_grow_workspace_bytes,
+ *           8-byte aligned; its contents on entry do not matter
+ * 1 <= depth, 1 <= k <= 16, depth * k <= 256, k <= vocab <= 64 * 16384,
+ * 1 <= n <= depth * k, and fewer than 2^24 chunks of 16384 logits in all rows. */
+kvshot_status kvshot_tree_grow(const void* const* level_logits, int32_t dtype, int32_t batch, int32_t depth,
+                               int32_t vocab, int32_t k, int32_t n, int32_t* parents, int32_t* tokens,
+                               int32_t* depths, float* scores, void* workspace, int64_t workspace_bytes,
+                               void* stream);
+
 #ifdef __cplusplus
 }
 #endif

@@ -38,6 +38,7 @@ EXPORTED_SYMBOLS = [
     "kvshot_kvproj_set_option", "kvshot_kvproj_plan", "kvshot_kvproj_profile_read",
     "kvshot_acceptance_stats", "kvshot_topk_workspace_bytes", "kvshot_topk_logprobs", "kvshot_tree_expand", "kvshot_tree_select",
     "kvshot_tree_level_workspace_bytes", "kvshot_tree_level",
+    "kvshot_tree_grow_workspace_bytes", "kvshot_tree_grow",
 ]
 FUSION_CROSS_ONLY, FUSION_OUT_FP32 = 1, 2
 KVPROJ_ROPE = 1
@@ -142,6 +143,7 @@ def load_library(path: Optional[str] = None):
         "kvshot_tree_expand": [_i32, _i32, _i32, _i32] + [_vp] * 6 + [_vp],
         "kvshot_tree_select": [_i32, _i32, _i32, _i32] + [_vp] * 7 + [_vp],
         "kvshot_tree_level": [_vp, _i32, _i32, _i32, _i32, _i64, _i32] + [_vp] * 5 + [_i64, _vp],
+        "kvshot_tree_grow": [ctypes.POINTER(_vp)] + [_i32] * 6 + [_vp] * 5 + [_i64, _vp],
     }
     for name, args in sig.items():
         f = getattr(lib, name)
@@ -151,6 +153,8 @@ def load_library(path: Optional[str] = None):
     lib.kvshot_topk_workspace_bytes.restype = _i64
     lib.kvshot_tree_level_workspace_bytes.argtypes = [_i32, _i32, _i32]
     lib.kvshot_tree_level_workspace_bytes.restype = _i64
+    lib.kvshot_tree_grow_workspace_bytes.argtypes = [_i32, _i32, _i32, _i32]
+    lib.kvshot_tree_grow_workspace_bytes.restype = _i64
     lib.kvshot_status_string.argtypes = [_i32]
     lib.kvshot_status_string.restype = ctypes.c_char_p
     if path is None:
@@ -557,11 +561,28 @@ def tree_level(logits, scores, k: int, workspace=None, out=None, stream=None):
 def grow_tree(level_logits, k: int, n: int, stream=None):
     """Grow a tree level by level: ``level_logits[d]`` holds the drafter's logits for level d's frontier
     ([batch][1][vocab] for the root, then [batch][k][vocab], frontier nodes in the order the previous level
-    returned them).  Only sequences the library calls."""
+    returned them).  Only sequences the library calls: three launches when every level has the same type and
+    vocabulary, else one per level and the selection (the same tree)."""
     torch = _torch()
     batch = level_logits[0].shape[0]
     dev = level_logits[0].device
     depth = len(level_logits)
+    z0 = level_logits[0]
+    if z0.dtype in (torch.bfloat16, torch.float32) and z0.dim() == 3 and all(
+            z.is_cuda and z.device == dev and z.dtype == z0.dtype and z.is_contiguous()
+            and z.shape == (batch, k if d else 1, z0.shape[2]) for d, z in enumerate(level_logits)):
+        lib = load_library()
+        vocab = z0.shape[2]
+        need = lib.kvshot_tree_grow_workspace_bytes(batch, depth, k, vocab)
+        if need >= 0:
+            ws = torch.empty(need, dtype=torch.uint8, device=dev)
+            par, tok, dep = (torch.empty((batch, n), dtype=torch.int32, device=dev) for _ in range(3))
+            sc = torch.empty((batch, n), dtype=torch.float32, device=dev)
+            _check("kvshot_tree_grow", lib.kvshot_tree_grow(
+                (_vp * depth)(*[z.data_ptr() for z in level_logits]), BF16 if z0.dtype == torch.bfloat16 else FP32,
+                batch, depth, vocab, k, n, par.data_ptr(), tok.data_ptr(), dep.data_ptr(), sc.data_ptr(),
+                ws.data_ptr(), need, _stream_of(stream)))
+            return par, tok, dep, sc
     lpar = torch.empty((depth, batch, k), dtype=torch.int32, device=dev)
     ltok = torch.empty((depth, batch, k), dtype=torch.int32, device=dev)
     lsc = torch.empty((depth, batch, k), dtype=torch.float32, device=dev)

@@ -14,8 +14,8 @@
 //     every logit of the chunk's top k is >= T;
 //   * the logits >= T are appended to an LDS list, usually a few dozen, and
 //     ranked by counting the entries that beat each one.  Threads first
-//     append their groups of 8 logits whose max is >= T, and one thread per
-//     group then appends that group's logits >= T.  Should more than 256
+//     append their groups of 8 logits whose max is >= T, as they were read, and
+//     one thread per group then appends that group's logits >= T.  Should more than 256
 //     groups or 1024 logits pass (a flat distribution with many equal
 //     logits), k rounds of workgroup arg-max over the registers give the same
 //     k pairs.
@@ -32,6 +32,13 @@
 // kvshot_tree_level runs the same chunk workgroups in level mode: the last
 // chunk of each frontier row to finish merges that row, and the last merged
 // row of each sequence expands the frontier, so a whole level is one launch.
+//
+// kvshot_tree_grow has the logits of all levels at hand: one launch of the chunk
+// workgroups over the rows of every level (568 rows for 8 sequences, depth 8 and
+// k = 10, so the chip is full: 35 us for 173 MB, 4.9 TB/s, bound by about 650
+// vector instructions a wave, 64 exponentials among them), the merge, and one
+// workgroup per sequence for all expansions and the selection (11 us).  The whole
+// growth took 142 us level by level, 50 us so.
 //
 // kvshot_tree_expand / kvshot_tree_select: one workgroup of 256 threads per
 // sequence, one candidate per thread (at most 256).  Candidate c is ordered by
@@ -53,6 +60,8 @@ namespace {
 constexpr int kTopK = 16;                       // largest k
 constexpr int kMaxCand = 256;                   // candidates of one expansion or selection
 constexpr int kThreads = 256;
+constexpr int kGrowThreads = 1024;              // tree_grow_kernel: 16 waves rank a level's candidates
+constexpr int kSegKeys = 16;                    // keys a wave of it reads at a time
 constexpr int kPerThread = 64;                  // logits per thread, in registers
 constexpr int kChunk = kThreads * kPerThread;   // logits per workgroup
 constexpr int kMaxChunks = 64;                  // vocabulary <= 64 chunks
@@ -144,28 +153,6 @@ __device__ __forceinline__ float rescale(float s, float m, float M) {
   return m == -INFINITY ? 0.0f : s * __builtin_amdgcn_exp2f((m - M) * kLog2e);
 }
 
-// Room for `cnt` (0..8) entries of this lane in an LDS list whose length is
-// `*counter`: the lane's offset among the wave's requests from eight ballots
-// (lane L asks for more than b entries), then one atomic for the whole wave.
-// Called by every lane of the wave (uniform control flow).
-__device__ __forceinline__ int wave_alloc(int cnt, int* counter) {
-  const int lane = threadIdx.x & 63;
-  const uint64_t below = (1ull << lane) - 1ull;
-  int prefix = 0, total = 0;
-#pragma unroll
-  for (int b = 0; b < 8; ++b) {
-    const uint64_t m = __ballot(cnt > b);
-    prefix += __popcll(m & below);
-    total += __popcll(m);
-  }
-  int base = 0;
-  if (total > 0) {
-    if (lane == 0) base = atomicAdd(counter, total);
-    base = __builtin_amdgcn_readfirstlane(base);
-  }
-  return base + prefix;
-}
-
 // number of the n keys in LDS that beat `key`
 __device__ __forceinline__ int rank_of(const uint64_t* keys, int n, uint64_t key) {
   int rank = 0;
@@ -220,20 +207,18 @@ struct LevelArgs {
 // arrive (device-scope counters, no waiting) merges the row, and the last row
 // of a sequence expands the frontier.
 template <bool BF16, bool LEVEL>
-__global__ __launch_bounds__(kThreads) void topk_chunk_kernel(const void* logits, int vocab, int64_t row_stride, int k,
-                                                              int chunks, bool vec, int32_t* tokens,
-                                                              float* logprobs, uint64_t* ws, LevelArgs L) {
+__device__ __forceinline__ void topk_chunk(const void* logits, int vocab, int k, int chunks, bool vec, int row, int chunk,
+                                           int64_t row0, int32_t* tokens, float* logprobs, uint64_t* ws,
+                                           LevelArgs L) {
   __shared__ float row_m[16], row_s[16];
   __shared__ float sh_T, sh_M, sh_S;
   __shared__ uint64_t win[4];
   __shared__ uint64_t cand[kCandCap + 1];         // + a spare slot for writes that are thrown away
-  __shared__ float4 slot_v[kSlots][2];
+  __shared__ u32x4 slot_w[kSlots][BF16 ? 1 : 2];
   __shared__ int slot_t[kSlots];
   __shared__ int cand_n, slot_n;
   __shared__ int sh_last;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int row = blockIdx.x / chunks;
-  const int chunk = blockIdx.x - row * chunks;
   // Chunk c covers tokens [c * 16384, (c + 1) * 16384).  Where rows are 16-byte aligned and the
   // vocabulary is a multiple of 8 and at least one chunk long, a row's last chunk is read as the
   // 16384 tokens ending at the vocabulary's end, those of the previous chunk masked to -inf: every
@@ -243,51 +228,47 @@ __global__ __launch_bounds__(kThreads) void topk_chunk_kernel(const void* logits
   const bool shifted = vec && (vocab & 7) == 0 && vocab >= kChunk;
   const int lo = chunk * kChunk;                                   // first token of the chunk
   const int base = shifted ? min(lo, vocab - kChunk) : lo;         // first token read
-  float z[kPerThread];                                             // z[8g + e]: token base + 8 (256 g + tid) + e
-  const int64_t row0 = row * row_stride;
-  if (shifted) {
+  // This thread's logits as they were read: element 8 g + e is token base + 8 (256 g + tid) + e.  bf16
+  // pairs stay packed (32 registers instead of 64), which lets eight workgroups share a CU: the loads of
+  // some overlap the exponentials and the ranking of others.
+  constexpr int kWords = BF16 ? kPerThread / 2 : kPerThread;
+  uint32_t zw[kWords];
+  auto z = [&](int i) {
+    if constexpr (BF16) return __uint_as_float((i & 1) ? zw[i / 2] & 0xffff0000u : zw[i / 2] << 16);
+    else return __uint_as_float(zw[i]);
+  };
+  // between the phases below: values unpacked for one are not kept for the next
+  auto repack = [&]() {
     if constexpr (BF16) {
-      const uint16_t* r = (const uint16_t*)logits + row0 + base + 8 * tid;
-      u32x4 q[kPerThread / 8];
 #pragma unroll
-      for (int g = 0; g < kPerThread / 8; ++g) q[g] = *(const u32x4*)(r + 8 * kThreads * g);
-#pragma unroll
-      for (int g = 0; g < kPerThread / 8; ++g)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          z[8 * g + 2 * e] = __uint_as_float(q[g][e] << 16);
-          z[8 * g + 2 * e + 1] = __uint_as_float(q[g][e] & 0xffff0000u);
-        }
-    } else {
-      const float* r = (const float*)logits + row0 + base + 8 * tid;
-      float4 q[kPerThread / 4];
-#pragma unroll
-      for (int g = 0; g < kPerThread / 8; ++g) {
-        q[2 * g] = *(const float4*)(r + 8 * kThreads * g);
-        q[2 * g + 1] = *(const float4*)(r + 8 * kThreads * g + 4);
-      }
-#pragma unroll
-      for (int j = 0; j < kPerThread / 4; ++j) {
-        z[4 * j + 0] = q[j].x;
-        z[4 * j + 1] = q[j].y;
-        z[4 * j + 2] = q[j].z;
-        z[4 * j + 3] = q[j].w;
-      }
+      for (int i = 0; i < kWords; ++i) asm volatile("" : "+v"(zw[i]));
     }
-    if (base < lo) {                              // the last chunk: drop the previous chunk's tokens
-      const int keep = lo - base - 8 * tid;       // z[i] is kept iff 8 * 256 (i / 8) + i % 8 >= keep
+  };
+  constexpr uint32_t kNone = BF16 ? 0xff80ff80u : 0xff800000u;      // -inf
+  if (shifted) {
+    const uint32_t* r = (const uint32_t*)((const char*)logits + (row0 + base + 8 * tid) * (BF16 ? 2 : 4));
 #pragma unroll
-      for (int i = 0; i < kPerThread; ++i)
-        if (8 * kThreads * (i >> 3) + (i & 7) < keep) z[i] = -INFINITY;
+    for (int g = 0; g < kPerThread / 8; ++g)
+#pragma unroll
+      for (int j = 0; j < kWords / 32; ++j) {
+        const u32x4 q = *(const u32x4*)(r + kWords / 8 * kThreads * g + 4 * j);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) zw[kWords / 8 * g + 4 * j + e] = q[e];
+      }
+    if (base < lo) {                              // the last chunk: drop the previous chunk's tokens
+      const int keep = lo - base - 8 * tid;       // element i is kept iff 8 * 256 (i / 8) + i % 8 >= keep;
+#pragma unroll                                    // keep is a multiple of 8 (a vocabulary of whole groups)
+      for (int i = 0; i < kPerThread; i += BF16 ? 2 : 1)
+        if (8 * kThreads * (i >> 3) + (i & 7) < keep) zw[BF16 ? i / 2 : i] = kNone;
     }
   } else {
 #pragma unroll
     for (int g = 0; g < kPerThread / 8; ++g) {
-      uint32_t raw[8];                            // loaded first, converted after: eight loads in flight
+      uint32_t raw[8];                            // loaded first, packed after: eight loads in flight
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
         const int t = base + 8 * (kThreads * g + tid) + e;
-        raw[e] = BF16 ? 0xff80u : 0xff800000u;    // -inf
+        raw[e] = BF16 ? 0xff80u : kNone;
         if (t < vocab) {
           if constexpr (BF16)
             raw[e] = ((const uint16_t*)logits)[row0 + t];
@@ -296,10 +277,11 @@ __global__ __launch_bounds__(kThreads) void topk_chunk_kernel(const void* logits
         }
       }
 #pragma unroll
-      for (int e = 0; e < 8; ++e) z[8 * g + e] = __uint_as_float(BF16 ? raw[e] << 16 : raw[e]);
+      for (int e = 0; e < kWords / 8; ++e)
+        zw[kWords / 8 * g + e] = BF16 ? raw[(2 * e) & 7] | raw[(2 * e + 1) & 7] << 16 : raw[e];
     }
   }
-  // token of z[i] = tbase + off(i), off(i) a constant of the unrolled loops; comparisons of tokens are
+  // token of z(i) = tbase + off(i), off(i) a constant of the unrolled loops; comparisons of tokens are
   // made on offsets so that no per-element token is ever held in a register
   const int tbase = base + 8 * tid;
   auto off = [](int i) { return 8 * kThreads * (i >> 3) + (i & 7); };
@@ -309,17 +291,19 @@ __global__ __launch_bounds__(kThreads) void topk_chunk_kernel(const void* logits
   float mt = -INFINITY;
 #pragma unroll
   for (int g = 0; g < kPerThread / 8; ++g) {
-    gm[g] = z[8 * g];
+    gm[g] = z(8 * g);
 #pragma unroll
-    for (int e = 1; e < 8; ++e) gm[g] = fmaxf(gm[g], z[8 * g + e]);
+    for (int e = 1; e < 8; ++e) gm[g] = fmaxf(gm[g], z(8 * g + e));
     mt = fmaxf(mt, gm[g]);
   }
+  repack();
   float st = 0.0f;
   if (mt != -INFINITY) {
     const float off = mt * kLog2e;
 #pragma unroll
-    for (int i = 0; i < kPerThread; ++i) st += __builtin_amdgcn_exp2f(fmaf(z[i], kLog2e, -off));
+    for (int i = 0; i < kPerThread; ++i) st += __builtin_amdgcn_exp2f(fmaf(z(i), kLog2e, -off));
   }
+  repack();
   const float mr = row_max(mt);
   const float sr = row_sum(rescale(st, mt, mr));
   if ((lane & 15) == 0) {
@@ -353,22 +337,23 @@ __global__ __launch_bounds__(kThreads) void topk_chunk_kernel(const void* logits
   const float T = fmaxf(sh_T, -FLT_MAX);           // never below the smallest logit: -inf never passes
 
   // logits >= T into the LDS list, in two steps that spread the work over the threads: every
-  // thread appends its groups of 8 whose max is >= T (the 8 logits and the first token) to a slot
-  // list; then thread t turns slot t into the keys of its logits >= T.
-  int gcnt = 0;
+  // thread appends its groups of 8 whose max is >= T (the 8 logits as they were read and the first
+  // token) to a slot list; then thread t turns slot t into the keys of its logits >= T.  A few of the
+  // threads append anything, so each takes its room with an atomic of its own (a prefix over the wave's
+  // lanes would cost all of them some 50 instructions); the lists' order does not matter.
   if (mt >= T) {
+    int gcnt = 0;
 #pragma unroll
     for (int g = 0; g < kPerThread / 8; ++g) gcnt += gm[g] >= T ? 1 : 0;
-  }
-  int p_slot = wave_alloc(gcnt, &slot_n);
-  if (gcnt > 0) {
-    int p = p_slot;
+    int p = atomicAdd(&slot_n, gcnt);
 #pragma unroll
     for (int g = 0; g < kPerThread / 8; ++g)
       if (gm[g] >= T) {
         if (p < kSlots) {
-          slot_v[p][0] = float4{z[8 * g], z[8 * g + 1], z[8 * g + 2], z[8 * g + 3]};
-          slot_v[p][1] = float4{z[8 * g + 4], z[8 * g + 5], z[8 * g + 6], z[8 * g + 7]};
+#pragma unroll
+          for (int j = 0; j < kWords / 32; ++j)
+            slot_w[p][j] = u32x4{zw[kWords / 8 * g + 4 * j], zw[kWords / 8 * g + 4 * j + 1],
+                                 zw[kWords / 8 * g + 4 * j + 2], zw[kWords / 8 * g + 4 * j + 3]};
           slot_t[p] = tbase + off(8 * g);
         }
         ++p;
@@ -376,23 +361,31 @@ __global__ __launch_bounds__(kThreads) void topk_chunk_kernel(const void* logits
   }
   __syncthreads();
   const int ns = slot_n;
-  if (ns <= kSlots && (tid & ~63) < ns) {         // waves that hold a slot (wave-uniform)
-    const bool mine = tid < ns;
-    const float4 a = mine ? slot_v[tid][0] : float4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
-    const float4 c = mine ? slot_v[tid][1] : float4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
-    const float v[8] = {a.x, a.y, a.z, a.w, c.x, c.y, c.z, c.w};
+  if (ns <= kSlots && tid < ns) {
+    float v[8];
+#pragma unroll
+    for (int j = 0; j < kWords / 32; ++j) {
+      const u32x4 q = slot_w[tid][j];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        if constexpr (BF16) {
+          v[2 * e] = __uint_as_float(q[e] << 16);
+          v[2 * e + 1] = __uint_as_float(q[e] & 0xffff0000u);
+        } else {
+          v[4 * j + e] = __uint_as_float(q[e]);
+        }
+      }
+    }
     int cnt = 0;
 #pragma unroll
     for (int e = 0; e < 8; ++e) cnt += v[e] >= T ? 1 : 0;
-    int p = wave_alloc(cnt, &cand_n);
-    if (mine) {
-      const int t0 = slot_t[tid];
+    int p = atomicAdd(&cand_n, cnt);
+    const int t0 = slot_t[tid];
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {               // branch-free: a logit below T goes to the spare slot
-        const bool pass = v[e] >= T;
-        cand[pass && p < kCandCap ? p : kCandCap] = pair_key(v[e], t0 + e);
-        p += pass ? 1 : 0;
-      }
+    for (int e = 0; e < 8; ++e) {                 // branch-free: a logit below T goes to the spare slot
+      const bool pass = v[e] >= T;
+      cand[pass && p < kCandCap ? p : kCandCap] = pair_key(v[e], t0 + e);
+      p += pass ? 1 : 0;
     }
   }
   __syncthreads();
@@ -426,11 +419,12 @@ __global__ __launch_bounds__(kThreads) void topk_chunk_kernel(const void* logits
     int li = -1;
     for (int r = 0; r < k; ++r) {
       const int lrel = li - tbase;
+      repack();
       float bv = -INFINITY;
       int bi = -1;                                // element index: tokens rise with it, so the first of equal
 #pragma unroll                                    // values is the best and a later equal one never replaces it
       for (int i = 0; i < kPerThread; ++i) {
-        const float v = z[i];
+        const float v = z(i);
         const bool after = (v < lv) | ((v == lv) & (off(i) > lrel));
         if (after & (v > bv)) {                   // v > bv >= -inf: only logits
           bv = v;
@@ -539,6 +533,33 @@ __global__ __launch_bounds__(kThreads) void topk_chunk_kernel(const void* logits
   if (tid == 0) atomicExch(seq_counter, 0u);      // ready for the next call
 }
 
+template <bool BF16, bool LEVEL>
+__global__ __launch_bounds__(kThreads) void topk_chunk_kernel(const void* logits, int vocab, int64_t row_stride, int k,
+                                                              int chunks, bool vec, int32_t* tokens,
+                                                              float* logprobs, uint64_t* ws, LevelArgs L) {
+  const int row = blockIdx.x / chunks;
+  topk_chunk<BF16, LEVEL>(logits, vocab, k, chunks, vec, row, blockIdx.x - row * chunks, row * row_stride, tokens,
+                          logprobs, ws, L);
+}
+
+// The logits of every level of a growth, each [batch][frontier][vocab] with a frontier of 1, then k.
+struct GrowLevels {
+  const void* p[kMaxCand];
+};
+
+// Top-k mode over the rows of all levels, level by level: level 0 has `batch` rows, the others batch * k.
+template <bool BF16>
+__global__ __launch_bounds__(kThreads) void topk_grow_kernel(GrowLevels levels, int batch, int vocab, int k, int chunks,
+                                                             int32_t* tokens, float* logprobs, uint64_t* ws) {
+  const int row = blockIdx.x / chunks;
+  const int level = row < batch ? 0 : 1 + (row - batch) / (batch * k);
+  const int in_level = row < batch ? row : (row - batch) - (level - 1) * batch * k;
+  const void* z = levels.p[level];
+  const bool vec = ((uintptr_t)z & 15) == 0 && vocab % (BF16 ? 8 : 4) == 0;
+  topk_chunk<BF16, false>(z, vocab, k, chunks, vec, row, blockIdx.x - row * chunks, (int64_t)in_level * vocab, tokens,
+                          logprobs, ws, LevelArgs{});
+}
+
 // One row of several chunks: combine the chunks' log-sum-exp parts and rank
 // their k best keys.
 __global__ __launch_bounds__(kThreads) void topk_merge_kernel(int k, int chunks, const uint64_t* ws, int32_t* tokens,
@@ -597,21 +618,16 @@ __global__ __launch_bounds__(kThreads) void tree_expand_kernel(int frontier, int
   }
 }
 
-__global__ __launch_bounds__(kThreads) void tree_select_kernel(int depth, int k, int n, const int32_t* level_parent,
-                                                               const int32_t* level_tokens, const float* level_scores,
-                                                               int32_t* parents, int32_t* tokens, int32_t* depths,
-                                                               float* scores) {
+// The n best of C = depth * k candidates as a tree, one candidate c = (depth d, rank i) per thread: score
+// sc, parent par in the level before, token tok.  Threads past kMaxCand only take part in the barriers.
+__device__ __forceinline__ void select_nodes(int b, int C, int k, int n, float sc, int par, int tok, int32_t* parents,
+                                             int32_t* tokens, int32_t* depths, float* scores) {
   __shared__ uint64_t keys[kMaxCand];
   __shared__ int pos[kMaxCand];
   __shared__ int wave_kept[4];
-  const int b = blockIdx.x, c = threadIdx.x, lane = c & 63, w = c >> 6;
-  const int C = depth * k;
-  // candidate c = (depth d, rank i) of sequence b sits at level block d: [depth][batch][k]
-  const int64_t at = ((int64_t)(c / k) * gridDim.x + b) * k + c % k;
-  float sc = 0.0f;
+  const int c = threadIdx.x, lane = c & 63, w = c >> 6;
   uint64_t key = 0ull;
   if (c < C) {
-    sc = level_scores[at];
     key = pair_key(sc, c);
     keys[c] = key;
   }
@@ -619,22 +635,118 @@ __global__ __launch_bounds__(kThreads) void tree_select_kernel(int depth, int k,
   const bool kept = c < C && rank_of(keys, C, key) < n;
   // output position: kept candidates before c, in (depth, rank) order
   const uint64_t mask = __ballot(kept);
-  if (lane == 0) wave_kept[w] = __popcll(mask);
+  if (lane == 0 && w < 4) wave_kept[w] = __popcll(mask);
   __syncthreads();
   int p = __popcll(mask & ((1ull << lane) - 1ull));
-  for (int j = 0; j < w; ++j) p += wave_kept[j];
+  for (int j = 0; j < min(w, 4); ++j) p += wave_kept[j];
   if (c < kMaxCand) pos[c] = kept ? p : -1;
   __syncthreads();
   if (kept) {
     const int d = c / k;
-    int par = level_parent[at];
     par = par < 0 ? 0 : (par >= k ? k - 1 : par);
     const int64_t o = (int64_t)b * n + p;
     parents[o] = d == 0 ? -1 : pos[(d - 1) * k + par];
-    tokens[o] = level_tokens[at];
+    tokens[o] = tok;
     depths[o] = d;
     scores[o] = sc;
   }
+}
+
+__global__ __launch_bounds__(kThreads) void tree_select_kernel(int depth, int k, int n, const int32_t* level_parent,
+                                                               const int32_t* level_tokens, const float* level_scores,
+                                                               int32_t* parents, int32_t* tokens, int32_t* depths,
+                                                               float* scores) {
+  const int b = blockIdx.x, c = threadIdx.x;
+  const int C = depth * k;
+  // candidate c = (depth d, rank i) of sequence b sits at level block d: [depth][batch][k]
+  const int64_t at = ((int64_t)(c / k) * gridDim.x + b) * k + c % k;
+  const bool in = c < C;
+  select_nodes(b, C, k, n, in ? level_scores[at] : 0.0f, in ? level_parent[at] : 0, in ? level_tokens[at] : 0, parents,
+               tokens, depths, scores);
+}
+
+// Every expansion of one sequence and the selection, from the top-k rows of all levels (topk_grow_kernel's
+// order), one candidate (frontier node, proposal rank) per thread.  A level depends on the one before it:
+// 1.05 us for 100 candidates, 0.8 us of it their ranking, where a launch of its own took 15 to 17 us.
+// (Ranking on one wave without workgroup barriers, after a bound that leaves 15 to 25 candidates, took
+// 1.2 us a level: the chain of dependent LDS reads is longer.)
+__global__ __launch_bounds__(kGrowThreads) void tree_grow_kernel(int batch, int depth, int k, int n,
+                                                                 const int32_t* row_tokens,
+                                                                 const float* row_logprobs, int32_t* parents,
+                                                                 int32_t* tokens, int32_t* depths, float* scores) {
+  __shared__ float lp[kMaxCand * kTopK];
+  __shared__ int32_t tk[kMaxCand * kTopK];
+  __shared__ __align__(16) uint64_t keys[kMaxCand + kSegKeys];
+  __shared__ int ranks[kMaxCand];
+  __shared__ float lev_score[kMaxCand];
+  __shared__ int lev_parent[kMaxCand], lev_at[kMaxCand];   // lev_at: the proposal's place among this sequence's rows
+  const int b = blockIdx.x, tid = threadIdx.x;
+  const int C = depth * k;
+  // this sequence's rows: one of level 0, then k of each level (row r of it at LDS row r)
+  auto global_row = [&](int r) {
+    const int d = r == 0 ? 0 : 1 + (r - 1) / k;
+    return r == 0 ? (int64_t)b : (int64_t)batch + (int64_t)(d - 1) * batch * k + (int64_t)b * k + (r - 1 - (d - 1) * k);
+  };
+  const int rows = 1 + (depth - 1) * k;             // rows * k <= 256 * 16
+  for (int c = tid; c < rows * k; c += kGrowThreads) {
+    const int64_t g = global_row(c / k) * k + c % k;
+    lp[c] = row_logprobs[g];
+    tk[c] = row_tokens[g];
+  }
+  if (tid < kMaxCand) ranks[tid] = 0;
+  for (int c = tid; c < kMaxCand + kSegKeys; c += kGrowThreads) keys[c] = 0ull;       // beats nothing
+  // Candidate c = (frontier node f, proposal i) for threads c < k * k.  Ranking a level: the waves split
+  // into groups of 64 candidates and, within a group, segments of the keys to compare with, 16 keys (eight
+  // 16-byte LDS reads of one address) in flight; the segments' counts add up in LDS.
+  const int f = tid / k, i = tid - f * k;
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  __syncthreads();
+  for (int d = 0; d < depth; ++d) {
+    const int cands = d == 0 ? k : k * k;
+    const int at = ((d == 0 ? 0 : 1 + (d - 1) * k) + f) * k + i;
+    float sc = 0.0f;
+    if (tid < cands) {
+      sc = (d == 0 ? 0.0f : lev_score[(d - 1) * k + f]) + lp[at];
+      keys[tid] = pair_key(sc, tid);
+    }
+    __syncthreads();
+    // 16, 8 or 4 segments for 1, 2 or up to 4 groups of candidates
+    const int shift = cands <= 64 ? 4 : (cands <= 128 ? 3 : 2);
+    const int group = wave >> shift;
+    const int len = (((cands + (1 << shift) - 1) >> shift) + 1) & ~1;                 // even, at most 64
+    const int first = (wave & ((1 << shift) - 1)) * len;
+    const int c = group * 64 + lane;
+    if (first < cands) {
+      const uint64_t mine = keys[c];
+      int beat = 0;
+      for (int j0 = 0; j0 < len; j0 += kSegKeys) {
+        uint64_t other[kSegKeys];
+#pragma unroll
+        for (int j = 0; j < kSegKeys; j += 2) {
+          const u32x4 q = *(const u32x4*)&keys[first + j0 + j];
+          other[j] = ((uint64_t)q[1] << 32) | q[0];
+          other[j + 1] = ((uint64_t)q[3] << 32) | q[2];
+        }
+#pragma unroll
+        for (int j = 0; j < kSegKeys; ++j) beat += (other[j] > mine && j0 + j < len) ? 1 : 0;
+      }
+      if (c < cands && beat) atomicAdd(&ranks[c], beat);
+    }
+    __syncthreads();
+    if (tid < cands) {
+      const int rank = ranks[tid];
+      ranks[tid] = 0;
+      if (rank < k) {
+        lev_score[d * k + rank] = sc;
+        lev_parent[d * k + rank] = f;
+        lev_at[d * k + rank] = at;
+      }
+    }
+    __syncthreads();
+  }
+  const bool in = tid < C;
+  const int tok = in ? tk[lev_at[tid]] : 0;
+  select_nodes(b, C, k, n, in ? lev_score[tid] : 0.0f, in ? lev_parent[tid] : 0, tok, parents, tokens, depths, scores);
 }
 
 bool aligned(const void* p, unsigned a) { return ((uintptr_t)p % a) == 0; }
@@ -746,5 +858,52 @@ extern "C" kvshot_status kvshot_tree_select(int32_t batch, int32_t depth, int32_
     return KVSHOT_ERR_INVALID_ARG;
   hipLaunchKernelGGL(tree_select_kernel, dim3(batch), dim3(kThreads), 0, (hipStream_t)stream, (int)depth, (int)k, (int)n,
                      level_parent, level_tokens, level_scores, parents, tokens, depths, scores);
+  return hipGetLastError() == hipSuccess ? KVSHOT_OK : KVSHOT_ERR_DEVICE;
+}
+
+namespace {
+int64_t grow_rows(int32_t batch, int32_t depth, int32_t k) { return (int64_t)batch * (1 + (int64_t)(depth - 1) * k); }
+}  // namespace
+
+extern "C" int64_t kvshot_tree_grow_workspace_bytes(int32_t batch, int32_t depth, int32_t k, int32_t vocab) {
+  if (batch < 1 || depth < 1 || k < 1 || k > kTopK || (int64_t)depth * k > kMaxCand || vocab < k ||
+      chunks_for(vocab) > kMaxChunks)
+    return -1;
+  const int64_t rows = grow_rows(batch, depth, k), chunks = chunks_for(vocab);
+  if (rows * chunks >= (1ll << 24)) return -1;      // a launch of 256 threads each
+  return (chunks == 1 ? 0 : rows * chunks * kRecord * (int64_t)sizeof(uint64_t)) + rows * k * 8;
+}
+
+extern "C" kvshot_status kvshot_tree_grow(const void* const* level_logits, int32_t dtype, int32_t batch, int32_t depth,
+                                          int32_t vocab, int32_t k, int32_t n, int32_t* parents, int32_t* tokens,
+                                          int32_t* depths, float* scores, void* workspace, int64_t workspace_bytes,
+                                          void* stream) {
+  if (!level_logits || !parents || !tokens || !depths || !scores || !workspace) return KVSHOT_ERR_INVALID_ARG;
+  if (dtype != KVSHOT_BF16 && dtype != KVSHOT_FP32) return KVSHOT_ERR_INVALID_ARG;
+  const int64_t need = kvshot_tree_grow_workspace_bytes(batch, depth, k, vocab);
+  if (need < 0 || workspace_bytes < need || !aligned(workspace, 8) || n < 1 || n > depth * k)
+    return KVSHOT_ERR_INVALID_ARG;
+  GrowLevels levels{};
+  for (int d = 0; d < depth; ++d) {
+    if (!level_logits[d] || !aligned(level_logits[d], dtype == KVSHOT_BF16 ? 2u : 4u)) return KVSHOT_ERR_INVALID_ARG;
+    levels.p[d] = level_logits[d];
+  }
+  const int rows = (int)grow_rows(batch, depth, k), chunks = chunks_for(vocab);
+  uint64_t* ws = (uint64_t*)workspace;              // chunk records, then the rows' tokens and log-probabilities
+  int32_t* row_tokens = (int32_t*)(chunks == 1 ? ws : ws + (int64_t)rows * chunks * kRecord);
+  float* row_logprobs = (float*)(row_tokens + (int64_t)rows * k);
+  hipStream_t s = (hipStream_t)stream;
+  const dim3 grid((unsigned)(rows * chunks));
+  if (dtype == KVSHOT_BF16)
+    hipLaunchKernelGGL((topk_grow_kernel<true>), grid, dim3(kThreads), 0, s, levels, (int)batch, (int)vocab, (int)k,
+                       chunks, row_tokens, row_logprobs, ws);
+  else
+    hipLaunchKernelGGL((topk_grow_kernel<false>), grid, dim3(kThreads), 0, s, levels, (int)batch, (int)vocab, (int)k,
+                       chunks, row_tokens, row_logprobs, ws);
+  if (chunks > 1)
+    hipLaunchKernelGGL(topk_merge_kernel, dim3(rows), dim3(kThreads), 0, s, (int)k, chunks, ws, row_tokens,
+                       row_logprobs);
+  hipLaunchKernelGGL(tree_grow_kernel, dim3(batch), dim3(kGrowThreads), 0, s, (int)batch, (int)depth, (int)k, (int)n,
+                     row_tokens, row_logprobs, parents, tokens, depths, scores);
   return hipGetLastError() == hipSuccess ? KVSHOT_OK : KVSHOT_ERR_DEVICE;
 }

@@ -431,3 +431,48 @@ def test_binding_rejects_bad_arguments():
     with pytest.raises(K().KvshotError):
         K().tree_expand(sc, t.zeros((2, 17, 4), dtype=t.int32, device="cuda"),
                         t.zeros((2, 17, 4), device="cuda"), 4)
+
+
+def _levels_on_device(seed, batch, depth, k, vocab, dtype, shift=0):
+    """Per-level logits; `shift` > 0 starts every second level that many elements into its buffer (unaligned rows)."""
+    out = []
+    for d in range(depth):
+        F = 1 if d == 0 else k
+        z = to_dev(W.draft_logits(seed, batch * F, vocab, dtype=dtype, stream=d), dtype)
+        if shift and d % 2:
+            buf = G.torch().empty(z.numel() + shift, dtype=z.dtype, device="cuda")
+            buf[shift:] = z.reshape(-1)
+            z = buf[shift:]
+        out.append(z.view(batch, F, vocab))
+    return out
+
+
+# one chunk and several, rows that are read with 16-byte loads and others, the smallest and largest frontiers
+# and depths (depth * k = 256, k * k = 256)
+@pytest.mark.parametrize("batch,depth,k,vocab,dtype,shift", [
+    (2, 8, 10, 40000, "bf16", 0), (1, 1, 1, 16, "fp32", 0), (3, 16, 16, 501, "bf16", 0), (2, 3, 7, 16384, "fp32", 0),
+    (1, 5, 16, 33333, "bf16", 0), (2, 4, 3, 32776, "bf16", 1), (1, 256, 1, 100, "fp32", 2), (5, 2, 2, 70000, "fp32", 0)])
+def test_grow_tree_in_three_launches_is_the_level_by_level_tree(batch, depth, k, vocab, dtype, shift):
+    m, t = K(), G.torch()
+    levels = _levels_on_device(91, batch, depth, k, vocab, dtype, shift)
+    n = min(60, depth * k)
+    lpar = t.empty((depth, batch, k), dtype=t.int32, device="cuda")
+    ltok, lsc = t.empty_like(lpar), t.empty((depth, batch, k), dtype=t.float32, device="cuda")
+    scores = t.zeros((batch, 1), dtype=t.float32, device="cuda")
+    for d, z in enumerate(levels):
+        m.tree_level(z, scores, k, out=(lpar[d], ltok[d], lsc[d]))
+        scores = lsc[d]
+    for got, ref in zip(m.grow_tree(levels, k, n), m.tree_select(lpar, ltok, lsc, n)):
+        assert t.equal(got, ref)
+
+
+def test_grow_tree_takes_levels_of_different_types():
+    m, t = K(), G.torch()
+    levels = _levels_on_device(92, 2, 3, 4, 20000, "bf16")
+    same = [z.float() for z in levels]
+    mixed = [levels[0], same[1], levels[2]]
+    for got, ref in zip(m.grow_tree(mixed, 4, 12), m.grow_tree(same, 4, 12)):
+        if got.dtype == t.int32:
+            assert t.equal(got, ref)
+        else:
+            assert (got - ref).abs().max() <= 1e-4
