@@ -65,11 +65,6 @@ __device__ __forceinline__ u32x4 bf16x8_sub(u32x4 o, u32x4 n) {
   return r;
 }
 
-__device__ __forceinline__ float sigmoidf_fast(float z) {
-  // 1 / (1 + 2^(-z log2 e)); saturates to exactly 0 and 1 for large |z|
-  return __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-z * 1.4426950408889634f));
-}
-
 // NSEG: segments of the reduction space this workgroup covers (4: all of
 // them; 2 or 1 when split).  Segment i of a split is seg0 + i; a split covers
 // the index range kbeg .. kbeg + d / kparts - 1 of its segments.  PF: chunks in

@@ -64,6 +64,7 @@ constexpr int kFusionBigTileMin = 128;
 // Both capped by the workspace.
 struct FusionPlan {
   int tile = kFusionTokens, splits = 1, kparts = 1, m_tiles = 0;
+  int slim = 0;        // output channels per workgroup of the slim kernel (16 or 32), 0: the tiled kernel
 };
 
 FusionPlan plan_tile(const kvshot_fusion_ctx* c, int tokens, int tile) {
@@ -84,7 +85,26 @@ FusionPlan plan_tile(const kvshot_fusion_ctx* c, int tokens, int tile) {
   return pl;
 }
 
+// Output channels per workgroup of the slim kernel for this call, or 0 where the tiled kernel serves it.
+// A CU holds one slim workgroup, so the grid should be one round: 16 channels while that gives at most a
+// workgroup per CU, else 32 (d = 4352, 64 tokens: 32.4 us with 136 workgroups of 32 channels, 48.7 us with
+// 272 of 16, 43.3 us tiled; d = 5120: 37.7, 55.9 and 49.1 us; d = 8192: 96.6 with 256 of 32, 112.6 us tiled).
+// Wider layers would need a second round of those too and keep the tiled kernel.  Every workgroup reads all activations, so the gain
+// shrinks with the tokens: d = 4096, packed weights, slim against tiled 27.0 and 33.0 us at 64 tokens, 36.1
+// and 40.9 us at 96, 42.8 and 38.4 us at 128.  32-channel workgroups hold at most 64 tokens' sums.
+int slim_channels(const kvshot_fusion_ctx* c, int tokens) {
+  if (c->opt_tile != 0 || c->opt_splits != 0) return 0;
+  if (c->d <= 16 * c->num_cus) return tokens <= kSlimTokens ? 16 : 0;
+  return tokens <= 64 && c->d <= 32 * c->num_cus ? 32 : 0;
+}
+
 FusionPlan make_plan(const kvshot_fusion_ctx* c, int tokens) {
+  if (const int channels = slim_channels(c, tokens)) {
+    FusionPlan pl;
+    pl.m_tiles = 1;
+    pl.slim = channels;
+    return pl;
+  }
   const FusionPlan small = plan_tile(c, tokens, kFusionTokens);
   if (c->opt_tile == 1 || c->opt_splits > 4) return small;
   const FusionPlan big = plan_tile(c, tokens, 128);
@@ -153,6 +173,7 @@ kvshot_status run_fusion(kvshot_fusion_handle h, int32_t tokens, const void* n, 
   p.splits = pl.splits;
   p.kparts = pl.kparts;
   p.tile_tokens = pl.tile;
+  p.tile_channels = pl.slim;
   // which partial planes each split writes: split s covers segments [seg0, seg0 + nseg)
   // (segments 0-2 feed the gate, segment 3 the delta projection)
   {
@@ -176,7 +197,7 @@ kvshot_status run_fusion(kvshot_fusion_handle h, int32_t tokens, const void* n, 
     slot->has_combine = p.splits > 1;
     if (hipEventRecord(slot->ev[0], s) != hipSuccess) return KVSHOT_ERR_DEVICE;
   }
-  if (launch_fusion(p, s) != hipSuccess) return KVSHOT_ERR_DEVICE;
+  if ((pl.slim ? launch_fusion_slim(p, s) : launch_fusion(p, s)) != hipSuccess) return KVSHOT_ERR_DEVICE;
   if (slot && hipEventRecord(slot->ev[1], s) != hipSuccess) return KVSHOT_ERR_DEVICE;
   if (p.splits > 1 && launch_fusion_combine(p, s) != hipSuccess) return KVSHOT_ERR_DEVICE;
   if (slot) {
@@ -294,7 +315,7 @@ kvshot_status kvshot_fusion_plan(kvshot_fusion_handle h, int32_t tokens, int32_t
   if (!h || tokens < 1 || tokens > h->max_tokens) return KVSHOT_ERR_INVALID_ARG;
   const FusionPlan pl = make_plan(h, tokens);
   if (splits) *splits = pl.splits;
-  if (workgroups) *workgroups = pl.m_tiles * (h->d / kFusionChannels) * pl.splits;
+  if (workgroups) *workgroups = pl.slim ? h->d / pl.slim : pl.m_tiles * (h->d / kFusionChannels) * pl.splits;
   return KVSHOT_OK;
 }
 

@@ -13,6 +13,7 @@ namespace kvshot {
 constexpr int kFusionTokens = 64;     // tokens per fusion workgroup (128 with the large-call tile)
 constexpr int kFusionChannels = 128;  // output channels per fusion workgroup
 constexpr int kFusionMaxSplits = 16;
+constexpr int kSlimTokens = 96;       // largest call of the slim kernel (few tokens, whole reduction in one workgroup)
 
 struct FusionParams {
   const uint16_t* n;            // [tokens][d] bf16
@@ -30,10 +31,17 @@ struct FusionParams {
   int32_t m_tiles, n_tiles, splits;
   int32_t kparts;               // reduction-index parts of a segment: splits / (segment groups)
   int32_t tile_tokens;          // tokens per workgroup tile: 64 or 128
+  int32_t tile_channels;        // slim kernel: output channels per workgroup, 16 or 32
   int32_t cross_only, out_fp32;
 };
 
+__device__ __forceinline__ float sigmoidf_fast(float z) {
+  // 1 / (1 + 2^(-z log2 e)); saturates to exactly 0 and 1 for large |z|
+  return __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-z * 1.4426950408889634f));
+}
+
 hipError_t launch_fusion(const FusionParams& p, hipStream_t s);
+hipError_t launch_fusion_slim(const FusionParams& p, hipStream_t s);
 hipError_t launch_fusion_combine(const FusionParams& p, hipStream_t s);
 hipError_t launch_fusion_pack(const uint16_t* w_g, const uint16_t* w_delta, uint16_t* packed, int d, hipStream_t s);
 

@@ -1,0 +1,281 @@
+// Gated delta fusion of calls with few tokens (at most 96) on bf16 MFMA (gfx950).
+//
+// Such a call streams 4 d^2 weights past a handful of activations, so the
+// weights' way from HBM bounds it and everything else has to stay out of that
+// stream's way.  A workgroup owns 16 (or 32) output channels and the whole
+// reduction: no partial sums go to memory and no second kernel runs.  Its NW waves share
+// the reduction out by 64-index chunks (wave w takes chunks w, w + NW, ...),
+// each with its own accumulators and its own LDS, so the loop has no barrier;
+// the waves' sums meet in LDS at the end, in wave order.
+//
+// Per chunk a wave loads the weights straight into MFMA operands
+// (v_mfma_f32_16x16x32_bf16, B operand: lane = channel % 16 + 16 * (k / 8 % 4)),
+// and n and o as whole 128-byte rows into registers, which it turns into A
+// operands (rows = tokens) through its LDS: loading the A operand directly
+// would put every lane on another row, and the CU then takes 37 GB/s from L2
+// instead of about 90.  The registers are the prefetch ring (PFA chunks of
+// activations, PFW of weights).
+//
+// The reduction uses W Delta = W o - W n: W_g3 and W_Delta meet o and n in
+// accumulators of their own, subtracted at the end.  Delta is then never
+// rounded to bf16, forming it costs no vector instructions (28 per operand,
+// 112 clocks, against two more products, 32 clocks), and o == n still gives
+// exactly zero, since both accumulators go through the same steps.
+//
+// Measured against the tiled kernel with split partials and its combine (us,
+// packed weights, d = 4096): 1 token 30.6 -> 20.3, 16 tokens 30.3 -> 21.0, 32
+// tokens 31.0 -> 22.9, 64 tokens 33.0 -> 27.0, 96 tokens 40.9 -> 36.1; 134 MB of
+// weights in 20.3 us are 6.6 TB/s.  What is left at 64 and 96 tokens is the
+// activations' way from L2: every workgroup reads all of n and o (1 MB at 64
+// tokens, beside 0.5 MB of weights).
+//
+// Rows past the last token repeat the last token's row; their outputs are not
+// stored and no other row sees them.
+#include "fusion_common.h"
+
+namespace kvshot {
+namespace {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+constexpr int kChunk = 64;                 // reduction indices per chunk (of each segment)
+
+__device__ __forceinline__ bf16x8 as_bf16x8(u32x4 v) { return __builtin_bit_cast(bf16x8, v); }
+
+__device__ __forceinline__ f32x4 mfma(u32x4 a, u32x4 b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(a), as_bf16x8(b), c, 0, 0, 0);
+}
+
+// Orders a wave's own LDS accesses (its lanes exchange data through LDS).
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// TB: 16-token blocks; CB: 16-channel blocks; CROSS: n is zero and its segment is skipped.
+template <int TB, int CB, int NW, int PFA, int PFW, bool PACKED, bool CROSS>
+__global__ __launch_bounds__(NW * 64, NW / 4) void fusion_slim_kernel(FusionParams p) {
+  static_assert(PFW % PFA == 0, "the loop is unrolled over the weight ring");
+  constexpr int TT = 16 * TB;
+  constexpr int kCh = 16 * CB;
+  constexpr int kMergePitch = kCh + 4;                     // floats per token row of the merge buffer: four rows shift by 16 banks
+  constexpr int kTensors = CROSS ? 1 : 2;                  // o, then n
+  constexpr int kRowLoads = TT / 8;                        // loads per tensor and chunk: 8 rows of 128 bytes each
+  constexpr int kSegs = CROSS ? 3 : 4;                     // W_g2, W_g3, W_Delta, then W_g1
+  constexpr int kWaveLds = TT * kChunk * kTensors;         // bf16 elements
+  constexpr int kMergeBytes = NW * 2 * TT * kMergePitch * 4;
+  constexpr int kLdsBytes = NW * kWaveLds * 2 > kMergeBytes ? NW * kWaveLds * 2 : kMergeBytes;
+  static_assert(kLdsBytes <= 160 * 1024, "LDS");
+  __shared__ __attribute__((aligned(16))) unsigned char lds[kLdsBytes];
+
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l16 = lane & 15;
+  const int g = lane >> 4;
+  const int d = p.d;
+  const int ct = CB * xcd_remap(blockIdx.x, gridDim.x);    // first 16-channel block: channels 16 ct .. 16 ct + kCh - 1
+  const int nchunks = d / kChunk;
+  const int count = (nchunks - w + NW - 1) / NW;           // chunks of this wave (d >= 256: waves past the last chunk have none)
+
+  // ---- operand addresses ----
+  // weights: piece (segment, chunk, i) of this lane covers k = 32 i + 8 g .. + 7 of channel 16 ct + l16.  Packed
+  // layout (1 KB per k-step of 32 channels): [channel tile of 128][segment][chunk][32 channels][k-step g][half i].
+  constexpr int kSegOf[4] = {1, 2, 3, 0};
+  const uint16_t* wbase[kSegs];
+#pragma unroll
+  for (int s = 0; s < kSegs; ++s) {
+    const int seg = kSegOf[s];
+    if constexpr (PACKED) {
+      wbase[s] = p.w_packed +
+                 ((((int64_t)(ct >> 3) * 4 + seg) * nchunks) * 4 + ((ct >> 1) & 3)) * 2048 + g * 512 +
+                 ((ct & 1) * 16 + l16) * 8;
+    } else {
+      const int64_t ch = 16 * ct + l16;
+      wbase[s] = (seg < 3 ? p.w_g + ch * 3 * d + (int64_t)seg * d : p.w_delta + ch * d) + 8 * g;
+    }
+  }
+  // activations: load j covers rows 8 j + lane / 8, 16-byte piece lane % 8
+  uint32_t aoff[kRowLoads];
+#pragma unroll
+  for (int j = 0; j < kRowLoads; ++j) {
+    const int m = min(8 * j + (lane >> 3), p.tokens - 1);
+    aoff[j] = (uint32_t)m * (uint32_t)d + 8 * (lane & 7);
+  }
+  // Refills past the wave's last chunk keep the pattern (so the wait counts stay exact) but all read one piece.
+  const int64_t cstride = PACKED ? 16 * 8 : (int64_t)16 * d;   // to the next channel block, in W_Delta (W_g: three times as far)
+  auto load_w = [&](int it, u32x4 (&dst)[kSegs][2][CB]) {
+    const bool ok = it < count;
+    const int c = ok ? w + NW * it : 0;
+#pragma unroll
+    for (int s = 0; s < kSegs; ++s)
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb) {
+          const int64_t at = PACKED ? (int64_t)c * 8192 + (ok ? i * 256 + cb * cstride : 0)
+                                    : c * kChunk + (ok ? i * 32 + cb * (kSegOf[s] < 3 ? 3 : 1) * cstride : 0);
+          dst[s][i][cb] = *(const u32x4*)(wbase[ok ? s : 0] + at);
+        }
+  };
+  auto load_a = [&](int it, u32x4 (&dst)[kTensors][kRowLoads]) {
+    const bool ok = it < count;
+    const int k0 = ok ? (w + NW * it) * kChunk : 0;
+#pragma unroll
+    for (int t = 0; t < kTensors; ++t)
+#pragma unroll
+      for (int j = 0; j < kRowLoads; ++j)
+        dst[t][j] = *(const u32x4*)((t == 0 ? p.o : p.n) + k0 + (ok ? aoff[j] : aoff[0]));
+  };
+
+  // ---- LDS: rows of 128 bytes, 16-byte piece q of row r in slot q ^ swz(r), swz(r) = (r ^ (r / 8 % 4)) % 8: the
+  // eight or sixteen rows that one cycle reads at one piece then cover all banks ----
+  uint16_t* const mine = (uint16_t*)lds + w * kWaveLds;
+  const int st_row = lane >> 3;
+  auto stage = [&](const u32x4 (&src)[kTensors][kRowLoads]) {
+#pragma unroll
+    for (int t = 0; t < kTensors; ++t)
+#pragma unroll
+      for (int j = 0; j < kRowLoads; ++j) {
+        const int slot = (lane & 7) ^ ((st_row ^ (j & 3)) & 7);
+        *(u32x4*)(mine + t * TT * kChunk + (8 * j + st_row) * kChunk + 8 * slot) = src[t][j];
+      }
+  };
+  const int swz = (l16 ^ (l16 >> 3)) & 7;                  // of row 16 b + l16: ^ 2 (b % 2)
+
+  f32x4 acc[TB][CB][CROSS ? 2 : 4];                        // gate, delta projection; then W_g3 n and W_Delta n
+#pragma unroll
+  for (int b = 0; b < TB; ++b)
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+      for (int a = 0; a < (CROSS ? 2 : 4); ++a) acc[b][cb][a] = f32x4{0.f, 0.f, 0.f, 0.f};
+  auto compute = [&](const u32x4 (&wr)[kSegs][2][CB]) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int b = 0; b < TB; ++b) {
+        const uint16_t* row = mine + (16 * b + l16) * kChunk + 8 * ((4 * i + g) ^ swz ^ (2 * (b & 1)));
+        const u32x4 fo = *(const u32x4*)row;
+        u32x4 fn;
+        if constexpr (!CROSS) fn = *(const u32x4*)(row + TT * kChunk);
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb) {
+          auto& z = acc[b][cb];
+          z[0] = mfma(fo, wr[0][i][cb], z[0]);
+          z[1] = mfma(fo, wr[2][i][cb], z[1]);
+          if constexpr (!CROSS) z[3] = mfma(fn, wr[2][i][cb], z[3]);
+          z[0] = mfma(fo, wr[1][i][cb], z[0]);
+          if constexpr (!CROSS) {
+            z[2] = mfma(fn, wr[1][i][cb], z[2]);
+            z[0] = mfma(fn, wr[3][i][cb], z[0]);
+          }
+        }
+      }
+  };
+
+  // ---- main loop ----
+  u32x4 areg[PFA][kTensors][kRowLoads];
+  u32x4 wreg[PFW][kSegs][2][CB];
+#pragma unroll
+  for (int u = 0; u < PFW; ++u) {
+    if (u < PFA) load_a(u, areg[u]);
+    load_w(u, wreg[u]);
+  }
+  for (int it0 = 0; it0 < count; it0 += PFW) {
+#pragma unroll
+    for (int u = 0; u < PFW; ++u) {
+      const int it = it0 + u;
+      if (it < count) stage(areg[u % PFA]);
+      wave_sync();
+      load_a(it + PFA, areg[u % PFA]);
+      if (it < count) compute(wreg[u]);
+      wave_sync();
+      load_w(it + PFW, wreg[u]);
+    }
+  }
+
+  // ---- the waves' sums: gate and delta projection, [wave][plane][token][channel] ----
+  __syncthreads();
+  float* const merge = (float*)lds;
+#pragma unroll
+  for (int b = 0; b < TB; ++b)
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const auto& z = acc[b][cb];
+        const int at = (16 * b + 4 * g + v) * kMergePitch + 16 * cb + l16;
+        merge[(2 * w) * TT * kMergePitch + at] = CROSS ? z[0][v] : z[0][v] - z[CROSS ? 0 : 2][v];
+        merge[(2 * w + 1) * TT * kMergePitch + at] = CROSS ? z[1][v] : z[1][v] - z[CROSS ? 1 : 3][v];
+      }
+  __syncthreads();
+  // two channels of a token per thread
+  for (int e = tid; e < TT * kCh / 2; e += NW * 64) {
+    const int m = e / (kCh / 2), c2 = 2 * (e % (kCh / 2));
+    if (m >= p.tokens) continue;
+    const int at = m * kMergePitch + c2;
+    float2 zg = make_float2(0.f, 0.f), zd = make_float2(0.f, 0.f);
+#pragma unroll
+    for (int k = 0; k < NW; ++k) {
+      const float2 a = *(const float2*)(merge + (2 * k) * TT * kMergePitch + at);
+      const float2 b = *(const float2*)(merge + (2 * k + 1) * TT * kMergePitch + at);
+      zg.x += a.x;
+      zg.y += a.y;
+      zd.x += b.x;
+      zd.y += b.y;
+    }
+    const int c = 16 * ct + c2;
+    const int64_t idx = (int64_t)m * d + c;
+    const float2 bias = *(const float2*)(p.b_g + c);
+    const uint32_t nn = CROSS ? 0u : *(const uint32_t*)(p.n + idx);
+    const float g0 = sigmoidf_fast(zg.x + bias.x), g1 = sigmoidf_fast(zg.y + bias.y);
+    const float h0 = bf16_lo(nn) + g0 * zd.x, h1 = bf16_hi(nn) + g1 * zd.y;
+    if (p.out_fp32) *(float2*)((float*)p.h + idx) = make_float2(h0, h1);
+    else *(uint32_t*)((uint16_t*)p.h + idx) = pack_bf16x2(h0, h1);
+    if (p.g_out) *(float2*)(p.g_out + idx) = make_float2(g0, g1);
+  }
+}
+
+template <int TB, int CB, int NW, int PFA, int PFW, bool PACKED>
+void launch_slim_t(const FusionParams& p, hipStream_t s) {
+  const dim3 grid((unsigned)(p.d / (16 * CB))), block(NW * 64);
+  if (p.cross_only) hipLaunchKernelGGL((fusion_slim_kernel<TB, CB, NW, PFA, PFW, PACKED, true>), grid, block, 0, s, p);
+  else hipLaunchKernelGGL((fusion_slim_kernel<TB, CB, NW, PFA, PFW, PACKED, false>), grid, block, 0, s, p);
+}
+
+// Waves and ring depths by token blocks and channels, the fastest of those measured (us at d = 4096, or
+// 5120 for 32 channels, packed; the instances hold one workgroup's waves per CU without spilling):
+//   16 x 16  8 waves 1,2: 21.0; 2,2: 21.1; 3,3: 21.8; 4,4: 21.9; 4 waves 4,4: 21.7
+//   32 x 16  8 waves 1,1: 22.9; 1,2: 23.5; 2,2: 24.2; 4 waves 4,4: 24.2
+//   64 x 16  4 waves 2,2: 26.6; 3,3: 28.0; 2,4: 28.1; 8 waves 1,2: 28.3
+//   96 x 16  4 waves 1,1: 36.1; 1,2: 36.2; 2,2: 41.4
+//   16 x 32  8 waves 2,2: 31.3; 4 waves 2,2: 30.6 (row-major weights 43.3 and 51.2)
+//   32 x 32  4 waves 2,2: 34.6; 4,4: 35.3; 8 waves 1,2: 34.5 (row-major 46.6, 47.3, 50.8)
+//   64 x 32  4 waves 1,1: 37.7; 1,2: 41.1 (row-major weights 61.8 and 55.0)
+template <bool PACKED>
+void launch_slim(const FusionParams& p, hipStream_t s) {
+  if (p.tile_channels == 16) {
+    if (p.tokens <= 16) launch_slim_t<1, 1, 8, 1, 2, PACKED>(p, s);
+    else if (p.tokens <= 32) launch_slim_t<2, 1, 8, 1, 1, PACKED>(p, s);
+    else if (p.tokens <= 64) launch_slim_t<4, 1, 4, 2, 2, PACKED>(p, s);
+    else launch_slim_t<6, 1, 4, 1, 1, PACKED>(p, s);
+  } else {
+    if (p.tokens <= 16) launch_slim_t<1, 2, 8, 2, 2, PACKED>(p, s);
+    else if (p.tokens <= 32) launch_slim_t<2, 2, 4, 2, 2, PACKED>(p, s);
+    else launch_slim_t<4, 2, 4, 1, PACKED ? 1 : 2, PACKED>(p, s);
+  }
+}
+
+}  // namespace
+
+hipError_t launch_fusion_slim(const FusionParams& p, hipStream_t s) {
+  if (p.w_packed) launch_slim<true>(p, s);
+  else launch_slim<false>(p, s);
+  return hipGetLastError();
+}
+
+}  // namespace kvshot

@@ -135,6 +135,34 @@ def test_fusion_tiles_agree_with_packed_weights_and_fp32_output(tile):
             check(a.cpu().numpy(), h_ref, True, f"fp32 tile {64 * tile} splits {splits}")
 
 
+@pytest.mark.parametrize("d,tokens", [(d, t) for d in (256, 768) for t in (1, 16, 17, 32, 33, 64, 65, 96)] +
+                         [(4352, t) for t in (5, 32, 64)])
+def test_fusion_few_token_kernel(d, tokens):
+    # one workgroup per 16 channels (32 when d / 16 exceeds the CUs) with the whole reduction: the edges of its
+    # token blocks, waves without a chunk (d = 256 has four) and uneven ones (d = 768 has twelve for eight waves),
+    # both weight layouts, the cross-only variant, and o == n, where the two halves of W Delta cancel exactly
+    from paper_2604_26412_amd import GatedDeltaFusion
+    c = W.fusion_case(tokens, d, seed=3 * tokens + d)
+    h_ref, g_ref = reference(c)
+    x_ref, _ = reference(c, cross_only=True)
+    with GatedDeltaFusion(d, tokens) as fz:
+        assert fz.plan(tokens) == dict(splits=1, workgroups=d // (16 if d <= 4096 else 32))
+        dv = upload(c)
+        t = G.torch()
+        packed = fz.pack_weights(dv["w_g"], dv["w_delta"])
+        h, g = run(fz, dv, c, out_dtype="fp32")
+        a = fz(dv["n"], dv["o"], None, dv["b_g"], None, packed=packed, out_dtype="fp32")
+        x, _ = run(fz, dv, c, cross_only=True)
+        b = fz(None, dv["o"], None, dv["b_g"], None, packed=packed, cross_only=True)
+        same = fz(dv["o"], dv["o"], None, dv["b_g"], None, packed=packed)
+        t.cuda.synchronize()
+    check(h, h_ref, True, f"few tokens {tokens} d={d}")
+    assert np.max(np.abs(g - g_ref)) <= 5e-3
+    check(x, x_ref, False, f"few tokens cross-only {tokens} d={d}")
+    assert np.array_equal(h, a.cpu().numpy()) and np.array_equal(x, b.float().cpu().numpy())
+    assert t.equal(same, dv["o"])
+
+
 @pytest.mark.parametrize("splits", [1, 8])
 def test_fusion_float32_output_and_gate(splits):
     from paper_2604_26412_amd import GatedDeltaFusion, OPT_SPLITS
