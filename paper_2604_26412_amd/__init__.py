@@ -167,9 +167,51 @@ def _check(fn: str, status: int):
         raise KvshotError(fn, status)
 
 
+_torch_module = None
+
+
 def _torch():
-    import torch
-    return torch
+    global _torch_module
+    if _torch_module is None:
+        import torch
+        _torch_module = torch
+    return _torch_module
+
+
+def _tensor_ptr(t, name, dtype, shape=None):
+    """``t.data_ptr()`` of a contiguous GPU tensor of this dtype (and shape, a tuple); raises otherwise."""
+    torch = _torch_module or _torch()
+    if not isinstance(t, torch.Tensor):
+        raise TypeError(f"{name} must be a torch tensor")
+    if not t.is_cuda:
+        raise ValueError(f"{name} must be on the GPU")
+    if t.dtype != dtype:
+        raise TypeError(f"{name} must be {dtype}, got {t.dtype}")
+    if not t.is_contiguous():
+        raise ValueError(f"{name} must be contiguous")
+    if shape is not None and t.shape != shape:
+        raise ValueError(f"{name} must have shape {shape}, got {tuple(t.shape)}")
+    return t.data_ptr()
+
+
+def _stream_of(stream):
+    """The given stream, or the current one of the current device as a raw pointer.  Asking for the pointer
+    takes 0.1 us, building a ``torch.cuda.Stream`` for it 1.5 us of a call that is 10 us on the host."""
+    if stream is not None:
+        return stream
+    torch = _torch_module or _torch()
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if raw is None:
+        return torch.cuda.current_stream().cuda_stream
+    return raw(torch.cuda.current_device())
+
+
+def _empty_rows(like, shape, dtype):
+    """An uninitialised contiguous tensor on ``like``'s device."""
+    torch = _torch_module or _torch()
+    if type(like) is torch.Tensor and like.dtype == dtype and like.shape == shape:
+        return torch.empty_like(like, memory_format=torch.contiguous_format)
+    return torch.empty(shape, dtype=dtype, device=like.device)
 
 
 def _dtype_code(name: str) -> int:
@@ -187,7 +229,7 @@ def stream_read(src, sink=None, workgroups: int = 2048, stream=None):
     if sink is None:
         sink = torch.empty(workgroups * 4, dtype=torch.int32, device=src.device)
     st = lib.kvshot_debug_stream_read(src.data_ptr(), src.numel() * src.element_size(), sink.data_ptr(), workgroups,
-                                      stream if stream is not None else torch.cuda.current_stream().cuda_stream)
+                                      _stream_of(stream))
     _check("kvshot_debug_stream_read", st)
     return sink
 
@@ -200,7 +242,7 @@ def mfma_rate(iters: int, workgroups: int = 256, sink=None, stream=None):
     if sink is None:
         sink = torch.empty(workgroups * 4, dtype=torch.int32, device="cuda")
     st = lib.kvshot_debug_mfma_rate(workgroups, iters, sink.data_ptr(),
-                                    stream if stream is not None else torch.cuda.current_stream().cuda_stream)
+                                    _stream_of(stream))
     _check("kvshot_debug_mfma_rate", st)
     return sink
 
@@ -227,6 +269,10 @@ class DraftAttention:
         self.cfg = cfg
         self.dtype = dtype
         self.out_dtype = out_dtype or dtype
+        # read on every call (a ctypes field costs ten times as much)
+        self._dims = (cfg.num_q_heads, cfg.num_kv_heads, cfg.head_dim, cfg.max_draft, cfg.max_pages_per_seq)
+        self._pool_elems = cfg.num_pages * (cfg.page_stride or cfg.num_kv_heads * cfg.page_size * cfg.head_dim)
+        self._max_ctx = cfg.max_pages_per_seq * cfg.page_size
         h = _vp()
         _check("kvshot_draft_attn_init", self._lib.kvshot_draft_attn_init(ctypes.byref(cfg), ctypes.byref(h)))
         self._h = h
@@ -254,56 +300,42 @@ class DraftAttention:
         torch = _torch()
         return torch.bfloat16 if self.dtype == "bf16" else torch.float32
 
-    def _tensor(self, t, name, dtype, shape=None, ndim=None):
-        torch = _torch()
-        if not isinstance(t, torch.Tensor):
-            raise TypeError(f"{name} must be a torch tensor")
-        if not t.is_cuda:
-            raise ValueError(f"{name} must be on the GPU")
-        if dtype is not None and t.dtype != dtype:
-            raise TypeError(f"{name} must be {dtype}, got {t.dtype}")
-        if not t.is_contiguous():
-            raise ValueError(f"{name} must be contiguous")
-        if shape is not None and tuple(t.shape) != tuple(shape):
-            raise ValueError(f"{name} must have shape {tuple(shape)}, got {tuple(t.shape)}")
-        if ndim is not None and t.dim() != ndim:
-            raise ValueError(f"{name} must have {ndim} dims")
-        return t.data_ptr()
+    @staticmethod
+    def _tensor(t, name, dtype, shape=None):
+        return _tensor_ptr(t, name, dtype, shape)
 
     def _common(self, q, k_pages, v_pages, page_table, ctx_lens, draft_k, draft_v, out, lse):
         torch = _torch()
-        c = self.cfg
         ed = self._elem_dtype()
         B, n = q.shape[0], q.shape[1]
-        D, Hq, Hkv = c.head_dim, c.num_q_heads, c.num_kv_heads
+        Hq, Hkv, D, max_draft, max_pages = self._dims
+        rows, draft = (B, n, Hq, D), (B, max_draft, Hkv, D)
         ptrs = dict(
-            q=self._tensor(q, "q", ed, (B, n, Hq, D)),
-            k=self._tensor(k_pages, "k_pages", ed),
-            v=self._tensor(v_pages, "v_pages", ed),
-            pt=self._tensor(page_table, "page_table", torch.int32, (B, c.max_pages_per_seq)),
-            lens=self._tensor(ctx_lens, "ctx_lens", torch.int32, (B,)),
-            dk=self._tensor(draft_k, "draft_k", ed, (B, c.max_draft, Hkv, D)),
-            dv=self._tensor(draft_v, "draft_v", ed, (B, c.max_draft, Hkv, D)),
+            q=_tensor_ptr(q, "q", ed, rows),
+            k=_tensor_ptr(k_pages, "k_pages", ed),
+            v=_tensor_ptr(v_pages, "v_pages", ed),
+            pt=_tensor_ptr(page_table, "page_table", torch.int32, (B, max_pages)),
+            lens=_tensor_ptr(ctx_lens, "ctx_lens", torch.int32, (B,)),
+            dk=_tensor_ptr(draft_k, "draft_k", ed, draft),
+            dv=_tensor_ptr(draft_v, "draft_v", ed, draft),
         )
-        if k_pages.numel() < c.num_pages * (c.page_stride or Hkv * c.page_size * D):
+        if k_pages.numel() < self._pool_elems:
             raise ValueError("k_pages smaller than num_pages pages")
-        if v_pages.numel() < c.num_pages * (c.page_stride or Hkv * c.page_size * D):
+        if v_pages.numel() < self._pool_elems:
             raise ValueError("v_pages smaller than num_pages pages")
         od = torch.bfloat16 if self.out_dtype == "bf16" else torch.float32
         if out is None:
-            out = torch.empty((B, n, Hq, D), dtype=od, device=q.device)
-        ptrs["out"] = self._tensor(out, "out", od, (B, n, Hq, D))
-        ptrs["lse"] = self._tensor(lse, "lse", torch.float32, (B, n, Hq)) if lse is not None else None
+            out = _empty_rows(q, rows, od)
+            ptrs["out"] = out.data_ptr()
+        else:
+            ptrs["out"] = _tensor_ptr(out, "out", od, rows)
+        ptrs["lse"] = _tensor_ptr(lse, "lse", torch.float32, rows[:3]) if lse is not None else None
         return ptrs, out
 
-    @staticmethod
-    def _stream(stream):
-        if stream is not None:
-            return stream
-        return _torch().cuda.current_stream().cuda_stream
+    _stream = staticmethod(_stream_of)
 
     def _hint(self, max_ctx):
-        return self.cfg.max_pages_per_seq * self.cfg.page_size if max_ctx is None else int(max_ctx)
+        return self._max_ctx if max_ctx is None else int(max_ctx)
 
     # -- calls -------------------------------------------------------------
     def step(self, q, k_pages, v_pages, page_table, ctx_lens, draft_k, draft_v, step_offsets, *, max_ctx=None,
@@ -436,7 +468,7 @@ def acceptance_stats(accepted, K: int, retention_step: Optional[int] = None, str
     lib = load_library()
     dev = accepted.device
     n = accepted.numel()
-    acc = GatedDeltaFusion._tensor(accepted, "accepted", torch.int32, (n,)) if n else None
+    acc = _tensor_ptr(accepted, "accepted", torch.int32, (n,)) if n else None
     counts = torch.empty((K + 1,), dtype=torch.int64, device=dev)
     alpha = torch.empty((K,), dtype=torch.float64, device=dev)
     mat = torch.empty((1,), dtype=torch.float64, device=dev)
@@ -444,12 +476,8 @@ def acceptance_stats(accepted, K: int, retention_step: Optional[int] = None, str
     _check("kvshot_acceptance_stats", lib.kvshot_acceptance_stats(
         acc, n, K, counts.data_ptr(), alpha.data_ptr(), mat.data_ptr(), ret.data_ptr() if ret is not None else None,
         retention_step if retention_step is not None else 0,
-        stream if stream is not None else torch.cuda.current_stream().cuda_stream))
+        _stream_of(stream)))
     return counts, alpha, mat, ret
-
-
-def _stream_of(stream):
-    return stream if stream is not None else _torch().cuda.current_stream().cuda_stream
 
 
 def topk_workspace_bytes(rows: int, vocab: int) -> int:
@@ -490,16 +518,16 @@ def tree_expand(scores, tokens, logprobs, k: int, out=None, stream=None):
     torch = _torch()
     lib = load_library()
     batch, frontier, proposals = tokens.shape
-    sc = GatedDeltaFusion._tensor(scores, "scores", torch.float32, (batch, frontier))
-    tk = GatedDeltaFusion._tensor(tokens, "tokens", torch.int32, (batch, frontier, proposals))
-    lp = GatedDeltaFusion._tensor(logprobs, "logprobs", torch.float32, (batch, frontier, proposals))
+    sc = _tensor_ptr(scores, "scores", torch.float32, (batch, frontier))
+    tk = _tensor_ptr(tokens, "tokens", torch.int32, (batch, frontier, proposals))
+    lp = _tensor_ptr(logprobs, "logprobs", torch.float32, (batch, frontier, proposals))
     if out is None:
         out = (torch.empty((batch, k), dtype=torch.int32, device=tokens.device),
                torch.empty((batch, k), dtype=torch.int32, device=tokens.device),
                torch.empty((batch, k), dtype=torch.float32, device=tokens.device))
     par, tok, nsc = out
     for t, name, dt in ((par, "parent", torch.int32), (tok, "token", torch.int32), (nsc, "score", torch.float32)):
-        GatedDeltaFusion._tensor(t, name, dt, (batch, k))
+        _tensor_ptr(t, name, dt, (batch, k))
     _check("kvshot_tree_expand", lib.kvshot_tree_expand(batch, frontier, proposals, k, sc, tk, lp, par.data_ptr(),
                                                         tok.data_ptr(), nsc.data_ptr(), _stream_of(stream)))
     return par, tok, nsc
@@ -511,9 +539,9 @@ def tree_select(level_parent, level_tokens, level_scores, n: int, stream=None):
     torch = _torch()
     lib = load_library()
     depth, batch, k = level_tokens.shape
-    lpar = GatedDeltaFusion._tensor(level_parent, "level_parent", torch.int32, (depth, batch, k))
-    ltok = GatedDeltaFusion._tensor(level_tokens, "level_tokens", torch.int32, (depth, batch, k))
-    lsc = GatedDeltaFusion._tensor(level_scores, "level_scores", torch.float32, (depth, batch, k))
+    lpar = _tensor_ptr(level_parent, "level_parent", torch.int32, (depth, batch, k))
+    ltok = _tensor_ptr(level_tokens, "level_tokens", torch.int32, (depth, batch, k))
+    lsc = _tensor_ptr(level_scores, "level_scores", torch.float32, (depth, batch, k))
     dev = level_tokens.device
     out = [torch.empty((batch, n), dtype=torch.int32, device=dev) for _ in range(3)]
     osc = torch.empty((batch, n), dtype=torch.float32, device=dev)
@@ -541,7 +569,7 @@ def tree_level(logits, scores, k: int, workspace=None, out=None, stream=None):
             or not logits.is_contiguous():
         raise ValueError("logits must be a contiguous bf16 or float32 device tensor [batch][frontier][vocab]")
     batch, frontier, vocab = logits.shape
-    sc = GatedDeltaFusion._tensor(scores, "scores", torch.float32, (batch, frontier))
+    sc = _tensor_ptr(scores, "scores", torch.float32, (batch, frontier))
     if workspace is None:
         workspace = tree_level_workspace(batch, frontier, vocab, logits.device)
     if out is None:
@@ -550,7 +578,7 @@ def tree_level(logits, scores, k: int, workspace=None, out=None, stream=None):
                torch.empty((batch, k), dtype=torch.float32, device=logits.device))
     par, tok, nsc = out
     for t, name, dt in ((par, "parent", torch.int32), (tok, "token", torch.int32), (nsc, "score", torch.float32)):
-        GatedDeltaFusion._tensor(t, name, dt, (batch, k))
+        _tensor_ptr(t, name, dt, (batch, k))
     _check("kvshot_tree_level", lib.kvshot_tree_level(
         logits.data_ptr(), BF16 if logits.dtype == torch.bfloat16 else FP32, batch, frontier, vocab, vocab, k, sc,
         par.data_ptr(), tok.data_ptr(), nsc.data_ptr(), workspace.data_ptr(),
@@ -628,18 +656,7 @@ class GatedDeltaFusion:
 
     @staticmethod
     def _tensor(t, name, dtype, shape):
-        torch = _torch()
-        if not isinstance(t, torch.Tensor):
-            raise TypeError(f"{name} must be a torch tensor")
-        if not t.is_cuda:
-            raise ValueError(f"{name} must be on the GPU")
-        if t.dtype != dtype:
-            raise TypeError(f"{name} must be {dtype}, got {t.dtype}")
-        if not t.is_contiguous():
-            raise ValueError(f"{name} must be contiguous")
-        if tuple(t.shape) != tuple(shape):
-            raise ValueError(f"{name} must have shape {tuple(shape)}, got {tuple(t.shape)}")
-        return t.data_ptr()
+        return _tensor_ptr(t, name, dtype, tuple(shape))
 
     def __call__(self, n, o, w_g, b_g, w_delta, *, out=None, gate=None, cross_only=False, out_dtype="bf16",
                  packed=None, stream=None):
@@ -651,23 +668,24 @@ class GatedDeltaFusion:
         bf = torch.bfloat16
         tokens, d = o.shape[0], self.d
         od = torch.bfloat16 if out_dtype in ("bf16", "bfloat16") else torch.float32
+        rows = (tokens, d)
         if out is None:
-            out = torch.empty((tokens, d), dtype=od, device=o.device)
-        n_ptr = None if (cross_only and n is None) else self._tensor(n, "n", bf, (tokens, d))
+            out = _empty_rows(o, rows, od)
+        n_ptr = None if (cross_only and n is None) else _tensor_ptr(n, "n", bf, rows)
         flags = (FUSION_CROSS_ONLY if cross_only else 0) | (FUSION_OUT_FP32 if od == torch.float32 else 0)
-        o_ptr = self._tensor(o, "o", bf, (tokens, d))
-        b_ptr = self._tensor(b_g, "b_g", torch.float32, (d,))
-        out_ptr = self._tensor(out, "out", od, (tokens, d))
-        g_ptr = self._tensor(gate, "gate", torch.float32, (tokens, d)) if gate is not None else None
-        s = stream if stream is not None else torch.cuda.current_stream().cuda_stream
+        o_ptr = _tensor_ptr(o, "o", bf, rows)
+        b_ptr = _tensor_ptr(b_g, "b_g", torch.float32, (d,))
+        out_ptr = _tensor_ptr(out, "out", od, rows)
+        g_ptr = _tensor_ptr(gate, "gate", torch.float32, rows) if gate is not None else None
+        s = _stream_of(stream)
         if packed is not None:
             _check("kvshot_gated_delta_fusion_packed", self._lib.kvshot_gated_delta_fusion_packed(
-                self._h, tokens, n_ptr, o_ptr, self._tensor(packed, "packed", bf, (4 * d * d,)), b_ptr, out_ptr,
+                self._h, tokens, n_ptr, o_ptr, _tensor_ptr(packed, "packed", bf, (4 * d * d,)), b_ptr, out_ptr,
                 g_ptr, flags, s))
         else:
             _check("kvshot_gated_delta_fusion", self._lib.kvshot_gated_delta_fusion(
-                self._h, tokens, n_ptr, o_ptr, self._tensor(w_g, "w_g", bf, (d, 3 * d)), b_ptr,
-                self._tensor(w_delta, "w_delta", bf, (d, d)), out_ptr, g_ptr, flags, s))
+                self._h, tokens, n_ptr, o_ptr, _tensor_ptr(w_g, "w_g", bf, (d, 3 * d)), b_ptr,
+                _tensor_ptr(w_delta, "w_delta", bf, (d, d)), out_ptr, g_ptr, flags, s))
         return out
 
     def pack_weights(self, w_g, w_delta, packed=None, stream=None):
@@ -680,7 +698,7 @@ class GatedDeltaFusion:
             self._h, self._tensor(w_g, "w_g", torch.bfloat16, (d, 3 * d)),
             self._tensor(w_delta, "w_delta", torch.bfloat16, (d, d)),
             self._tensor(packed, "packed", torch.bfloat16, (4 * d * d,)),
-            stream if stream is not None else torch.cuda.current_stream().cuda_stream))
+            _stream_of(stream)))
         return packed
 
     def set_option(self, option: int, value: int):
@@ -714,6 +732,9 @@ class KvProjection:
                                 page_size=page_size, max_pages_per_seq=max_pages_per_seq, num_pages=num_pages,
                                 dst_num_pages=dst_num_pages if dst_num_pages is not None else num_pages,
                                 max_tokens=max_tokens, max_position=max_position, rope_theta=rope_theta)
+        # read on every call (a ctypes field costs ten times as much)
+        c = self.cfg
+        self._pools = tuple((n, c.num_kv_heads, c.page_size, c.head_dim) for n in (c.num_pages, c.dst_num_pages))
         h = _vp()
         _check("kvshot_kvproj_init", self._lib.kvshot_kvproj_init(ctypes.byref(self.cfg), ctypes.byref(h)))
         self._h = h
@@ -735,20 +756,16 @@ class KvProjection:
     def __exit__(self, *a):
         self.close()
 
-    def _pool(self, t, name, npages):
-        shape = (npages, self.cfg.num_kv_heads, self.cfg.page_size, self.cfg.head_dim)
-        return GatedDeltaFusion._tensor(t, name, _torch().bfloat16, shape)
-
     def _tables(self, page_table, token_seq, token_pos, dst_page_table):
         torch = _torch()
         n = token_seq.shape[0]
         batch = page_table.shape[0]
         mp = self.cfg.max_pages_per_seq
-        pt = GatedDeltaFusion._tensor(page_table, "page_table", torch.int32, (batch, mp))
-        dpt = (GatedDeltaFusion._tensor(dst_page_table, "dst_page_table", torch.int32, (batch, mp))
+        pt = _tensor_ptr(page_table, "page_table", torch.int32, (batch, mp))
+        dpt = (_tensor_ptr(dst_page_table, "dst_page_table", torch.int32, (batch, mp))
                if dst_page_table is not None else None)
-        ts = GatedDeltaFusion._tensor(token_seq, "token_seq", torch.int32, (n,))
-        tp = GatedDeltaFusion._tensor(token_pos, "token_pos", torch.int32, (n,))
+        ts = _tensor_ptr(token_seq, "token_seq", torch.int32, (n,))
+        tp = _tensor_ptr(token_pos, "token_pos", torch.int32, (n,))
         return n, batch, pt, ts, tp, dpt
 
     def __call__(self, k_src, v_src, page_table, token_seq, token_pos, w_k, w_v, k_dst, v_dst, *,
@@ -759,14 +776,16 @@ class KvProjection:
         if len(k_src) != L or len(v_src) != L:
             raise ValueError(f"k_src and v_src must hold {L} pools")
         n, batch, pt, ts, tp, dpt = self._tables(page_table, token_seq, token_pos, dst_page_table)
-        ks = (_vp * L)(*[self._pool(t, f"k_src[{i}]", self.cfg.num_pages) for i, t in enumerate(k_src)])
-        vs = (_vp * L)(*[self._pool(t, f"v_src[{i}]", self.cfg.num_pages) for i, t in enumerate(v_src)])
-        d_kv = self.cfg.num_kv_heads * self.cfg.head_dim
-        wk = GatedDeltaFusion._tensor(w_k, "w_k", torch.bfloat16, (d_kv, L * d_kv))
-        wv = GatedDeltaFusion._tensor(w_v, "w_v", torch.bfloat16, (d_kv, L * d_kv))
-        kd = self._pool(k_dst, "k_dst", self.cfg.dst_num_pages)
-        vd = self._pool(v_dst, "v_dst", self.cfg.dst_num_pages)
-        s = stream if stream is not None else torch.cuda.current_stream().cuda_stream
+        bf = torch.bfloat16
+        src, dst = self._pools
+        ks = (_vp * L)(*[_tensor_ptr(t, f"k_src[{i}]", bf, src) for i, t in enumerate(k_src)])
+        vs = (_vp * L)(*[_tensor_ptr(t, f"v_src[{i}]", bf, src) for i, t in enumerate(v_src)])
+        d_kv = src[1] * src[3]
+        wk = _tensor_ptr(w_k, "w_k", bf, (d_kv, L * d_kv))
+        wv = _tensor_ptr(w_v, "w_v", bf, (d_kv, L * d_kv))
+        kd = _tensor_ptr(k_dst, "k_dst", bf, dst)
+        vd = _tensor_ptr(v_dst, "v_dst", bf, dst)
+        s = _stream_of(stream)
         _check("kvshot_kv_project", self._lib.kvshot_kv_project(
             self._h, n, batch, ks, vs, pt, ts, tp, wk, wv, kd, vd, dpt, KVPROJ_ROPE if rope else 0, s))
         return k_dst, v_dst
@@ -778,7 +797,7 @@ class KvProjection:
         bad, code = _i32(0), _i32(0)
         st = self._lib.kvshot_kv_project_validate(
             self._h, n, batch, pt, ts, tp, dpt, ctypes.byref(bad), ctypes.byref(code),
-            stream if stream is not None else torch.cuda.current_stream().cuda_stream)
+            _stream_of(stream))
         if st not in (KVSHOT_OK, 5):
             _check("kvshot_kv_project_validate", st)
         return st, bad.value, code.value
