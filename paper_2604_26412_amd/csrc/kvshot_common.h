@@ -147,23 +147,33 @@ struct BalancedSlot {
   int per;      // its blocks per split
   int first;    // exclusive prefix of split counts
 };
-// Wave-wide sum and prefix of small non-negative per-lane values (< 2^bits) from
-// bit-plane ballots: no cross-lane data movement through LDS, so no LDS latency
-// on the chain.
-__device__ __forceinline__ int wave_sum_small(int v, int bits) {
-  int total = 0;
-  for (int bit = 0; bit < bits; ++bit) total += __popcll(__ballot((v >> bit) & 1)) << bit;
-  return total;
+// Inclusive wave scans of non-negative per-lane values with the row-shift and row-broadcast forms of
+// the vector instructions: no cross-lane data movement through LDS, so no LDS latency on the chain.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp_or_zero(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xf, false);
 }
-__device__ __forceinline__ int wave_exclusive_prefix_small(int v, int bits, int lane) {
-  const uint64_t below = lane == 0 ? 0ull : (~0ull >> (64 - lane));   // lanes < lane
-  int pre = 0;
-  for (int bit = 0; bit < bits; ++bit) pre += __popcll(__ballot((v >> bit) & 1) & below) << bit;
-  return pre;
+__device__ __forceinline__ uint32_t wave_scan_add(uint32_t v) {
+  v += dpp_or_zero<0x111, 0xf>(v);   // row_shr 1, 2, 4, 8: scans of 16 lanes
+  v += dpp_or_zero<0x112, 0xf>(v);
+  v += dpp_or_zero<0x114, 0xf>(v);
+  v += dpp_or_zero<0x118, 0xf>(v);
+  v += dpp_or_zero<0x142, 0xa>(v);   // row_bcast 15 into rows 1 and 3
+  v += dpp_or_zero<0x143, 0xc>(v);   // row_bcast 31 into rows 2 and 3
+  return v;
+}
+__device__ __forceinline__ uint32_t wave_max(uint32_t v) {
+  v = max(v, dpp_or_zero<0x111, 0xf>(v));
+  v = max(v, dpp_or_zero<0x112, 0xf>(v));
+  v = max(v, dpp_or_zero<0x114, 0xf>(v));
+  v = max(v, dpp_or_zero<0x118, 0xf>(v));
+  v = max(v, dpp_or_zero<0x142, 0xa>(v));
+  v = max(v, dpp_or_zero<0x143, 0xc>(v));
+  return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
 }
 
-// ceil(a / c) for 0 <= a <= 2^25 and uniform c >= 1: a float reciprocal estimate (within one of the
-// quotient at these sizes), corrected by one
+// ceil(a / c) for 0 <= a <= 2^25 and c >= 1: a float reciprocal estimate, corrected by one.  Exact where
+// the quotient is below 2^20; above, still larger than 2^19.
 __device__ __forceinline__ int ceil_div_small(int a, int c, float rc) {
   const int num = a + c - 1;
   int q = (int)((float)num * rc);
@@ -181,22 +191,32 @@ __device__ __forceinline__ BalancedSlot balanced_schedule(const int32_t* ctx_len
     t = t > max_ctx ? max_ctx : t;
     nb = (t + kBlockKeys - 1) / kBlockKeys;
   }
-  // the longest prefix, by a bit-serial wave max (block counts <= 2^25: prefixes <= 2^30 keys)
-  int maxnb = 0;
-  for (int bit = 25; bit >= 0; --bit) {
-    const int cand = maxnb | (1 << bit);
-    if (__ballot(nb >= cand)) maxnb = cand;
-  }
-  // a sequence takes at most kMaxSplits items (what the combine merges)
-  auto splits_of = [&](int chunk, float rc) {
+  const uint32_t maxnb = wave_max((uint32_t)nb);
+  const uint32_t sum = (uint32_t)__builtin_amdgcn_readlane((int)wave_scan_add((uint32_t)nb), 63);   // <= 2^31
+  // a sequence takes at most kMaxSplits items (what the combine merges; larger quotients need not be exact)
+  auto splits_of = [&](int chunk) {
+    const float rc = __builtin_amdgcn_rcpf((float)chunk);
     return lane < batch ? min(kMaxSplits, max(1, ceil_div_small(nb, chunk, rc))) : 0;
   };
   auto total_splits = [&](int chunk) {
-    return wave_sum_small(splits_of(chunk, 1.0f / (float)chunk), 7);
+    return __builtin_amdgcn_readlane((int)wave_scan_add((uint32_t)splits_of(chunk)), 63);
   };
-  // chunk = min_chunk * k: the smallest k in [1, kmax] that fits (kmax covers the longest prefix)
-  const int kmax = max(1, (maxnb + min_chunk - 1) / min_chunk);
+  // chunk = min_chunk * k: the smallest k in [1, kmax] that fits (kmax covers the longest prefix).  The
+  // split counts sum to at least sum / chunk (where none is capped) and at most sum / chunk + batch, so
+  // that k lies between sum / (items min_chunk) and sum / ((items - batch) min_chunk): one or two steps
+  // of the search instead of eight, which every wave of the call waits for (2.5 us of a 62 us call).
+  const int kmax = max(1, ((int)maxnb + min_chunk - 1) / min_chunk);
   int lo = 1, hi = kmax;
+  if (items > batch) {
+    const float fsum = (float)sum;
+    const float least = fsum * __builtin_amdgcn_rcpf((float)items * (float)min_chunk);
+    const float most = fsum * __builtin_amdgcn_rcpf((float)(items - batch) * (float)min_chunk);
+    // both with a margin well above the rounding of these three operations
+    const int lo_est = (int)(least * (1.0f - 0x1p-18f));
+    if (most < (float)kmax) hi = min(hi, (int)(most * (1.0f + 0x1p-18f)) + 2);
+    // k = lo_est - 1 does not fit unless a count is capped there
+    if (lo_est > 1 && maxnb <= (uint64_t)kMaxSplits * (uint32_t)(lo_est - 1) * (uint32_t)min_chunk) lo = min(lo_est, hi);
+  }
   while (lo < hi) {
     const int mid = (lo + hi) >> 1;
     if (total_splits(mid * min_chunk) <= items) hi = mid;
@@ -205,9 +225,9 @@ __device__ __forceinline__ BalancedSlot balanced_schedule(const int32_t* ctx_len
   const int chunk = lo * min_chunk;
   BalancedSlot r;
   r.ctx = t;
-  r.splits = splits_of(chunk, 1.0f / (float)chunk);
+  r.splits = splits_of(chunk);
   r.per = lane < batch ? (nb + r.splits - 1) / r.splits : 0;
-  r.first = wave_exclusive_prefix_small(r.splits, 7, lane);
+  r.first = (int)wave_scan_add((uint32_t)r.splits) - r.splits;
   return r;
 }
 
