@@ -74,8 +74,9 @@ __global__ __launch_bounds__(NW * 64, WPS) void attn_mfma_kernel(AttnParams p) {
   constexpr int RW = RT / TPW;             // waves sharing one key stream's tiles
   constexpr int KS = NW / RW;              // key streams per workgroup
   constexpr int kLoadsPerWave = 8 / RW;    // 16-byte load instructions per K (and per V) tile and wave
+  constexpr bool kBalanced = NW == 1;      // one-wave workgroups: items of the length-balanced schedule
   static_assert(RW * TPW == RT && KS * RW == NW && kLoadsPerWave * RW == 8, "tile/wave configuration");
-  constexpr int kMergeBytes = (KS - 1) * RT * 64 * (64 * 4 + 8);
+  constexpr int kMergeBytes = KS > 1 ? KS * RT * 64 * (64 * 4 + 8) : 0;
   constexpr int kBufs = RW > 1 ? 2 : 1;    // waves that share tiles double-buffer them
   constexpr int kTileBytes = KS * kBufs * kStreamBytes;
   constexpr int kLdsBytes = kTileBytes > kMergeBytes ? kTileBytes : kMergeBytes;
@@ -91,7 +92,7 @@ __global__ __launch_bounds__(NW * 64, WPS) void attn_mfma_kernel(AttnParams p) {
   const int rg = wi % p.row_groups;
   wi /= p.row_groups;
   int h, item = 0;
-  if (!p.balanced) {
+  if constexpr (!kBalanced) {
     wi /= p.splits;                                // (split, KV head, sequence); the split is decoded below
     h = wi % p.hkv;
   } else {
@@ -101,14 +102,15 @@ __global__ __launch_bounds__(NW * 64, WPS) void attn_mfma_kernel(AttnParams p) {
 
   // One split: query rows of sequence b (prefix length T) against its target blocks [blk0, blk1),
   // plus its draft keys when `last`; written as part `part` of `nparts`, or as the output when
-  // nparts == 1.
+  // nparts == 1.  Where the work does not depend on the lengths (every sequence split alike), the page
+  // ids of the ring's first blocks (raw_ids) are loaded before T is known, and so is the step offset.
   auto segment = [&](const int b, const int T, const int part, const int nparts, const int blk0, const int blk1,
-                     const bool last) {
+                     const bool last, const int (&raw_ids)[PF], const int raw_s0) {
   const int nt = blk1 > blk0 ? blk1 - blk0 : 0;
 
   int s0 = 0, S = p.tree ? p.n_nodes : p.nq;
   if (!p.tree) {
-    s0 = p.step_offsets[b];
+    s0 = kBalanced ? p.step_offsets[b] : raw_s0;
     s0 = s0 < 0 ? 0 : (s0 > p.max_draft - p.nq ? p.max_draft - p.nq : s0);
     S = s0 + p.nq;
   }
@@ -187,7 +189,21 @@ __global__ __launch_bounds__(NW * 64, WPS) void attn_mfma_kernel(AttnParams p) {
   int idr[PF];                                     // page ids of the block each slot loads next
   if (nt > 0) {
 #pragma unroll
-    for (int u = 0; u < PF; ++u) idr[u] = load_ids(min(ks + KS * u, last_blk));
+    for (int u = 0; u < PF; ++u) {
+      if constexpr (kBalanced) {
+        idr[u] = load_ids(min(ks + KS * u, last_blk));
+      } else {
+        // as load_ids gives them: a block past the end is read as the last one, and the second half of
+        // the last block lies in the first half's page where the prefix ends before it
+        const int tb = ks + KS * u;
+        if (tb > last_blk) {
+          idr[u] = load_ids(last_blk);
+        } else {
+          const bool past = (((blk0 + tb) * kBlockKeys + 16) >> p.page_shift) > lp_last;
+          idr[u] = past ? __builtin_amdgcn_readlane(raw_ids[u], 0) : raw_ids[u];
+        }
+      }
+    }
 #pragma unroll
     for (int u = 0; u < PF; ++u) {
       issue_target(min(ks + KS * u, last_blk), idr[u], kst[u], vst[u]);
@@ -502,64 +518,74 @@ __global__ __launch_bounds__(NW * 64, WPS) void attn_mfma_kernel(AttnParams p) {
     l_row[i] = st[i].l + __shfl_xor(st[i].l, 32);
     M[i] = st[i].m;
   }
+  // channel tiles this wave writes out: all of them, or with several key streams its share of each row
+  // tile's four (every wave merges and stores a part, instead of one wave all of it)
+  constexpr int kOutTiles = 4 / KS;
+  f32x4 o[TPW][kOutTiles][4];
+  const int dt0 = KS > 1 ? ks * kOutTiles : 0;
   if constexpr (KS > 1) {
     static_assert(TPW == 1, "key streams are merged for one tile per wave");
     __syncthreads();
-    float* mo = (float*)lds;
-    float2* mml = (float2*)(lds + (KS - 1) * RT * 64 * 64 * 4);
-    if (ks > 0) {
-      const int slot = (ks - 1) * RT + rt;
+    f32x4* mo = (f32x4*)lds;                        // [stream][row tile][dt][q4][lane]
+    float2* mml = (float2*)(lds + KS * RT * 64 * 64 * 4);
+    const int slot = ks * RT + rt;
 #pragma unroll
-      for (int dt = 0; dt < 4; ++dt)
+    for (int dt = 0; dt < 4; ++dt)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) mo[(slot * 64 + dt * 16 + v) * 64 + lane] = oacc[0][dt][v];
-      mml[slot * 64 + lane] = make_float2(st[0].m, l_row[0]);
-    }
+      for (int q4 = 0; q4 < 4; ++q4)
+        mo[(slot * 16 + dt * 4 + q4) * 64 + lane] = f32x4{oacc[0][dt][q4 * 4 + 0], oacc[0][dt][q4 * 4 + 1],
+                                                          oacc[0][dt][q4 * 4 + 2], oacc[0][dt][q4 * 4 + 3]};
+    mml[slot * 64 + lane] = make_float2(st[0].m, l_row[0]);
     __syncthreads();
-    if (ks == 0) {
-      float mk[KS - 1], lk[KS - 1];
+    float mk[KS], lk[KS];
 #pragma unroll
-      for (int k = 0; k < KS - 1; ++k) {
-        const float2 t = mml[(k * RT + rt) * 64 + lane];
-        mk[k] = t.x;
-        lk[k] = t.y;
-        M[0] = fmaxf(M[0], t.x);
-      }
-      const float Mu = M[0] == -INFINITY ? 0.0f : M[0];
-      const float f0 = __builtin_amdgcn_exp2f(st[0].m - Mu);
-      l_row[0] *= f0;
-#pragma unroll
-      for (int dt = 0; dt < 4; ++dt)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) oacc[0][dt][v] *= f0;
-#pragma unroll
-      for (int k = 0; k < KS - 1; ++k) {
-        const float fk = __builtin_amdgcn_exp2f(mk[k] - Mu);
-        l_row[0] += lk[k] * fk;
-        const int slot = k * RT + rt;
-#pragma unroll
-        for (int dt = 0; dt < 4; ++dt)
-#pragma unroll
-          for (int v = 0; v < 16; ++v) oacc[0][dt][v] += mo[(slot * 64 + dt * 16 + v) * 64 + lane] * fk;
-      }
+    for (int k = 0; k < KS; ++k) {
+      const float2 t = mml[(k * RT + rt) * 64 + lane];
+      mk[k] = t.x;
+      lk[k] = t.y;
+      M[0] = fmaxf(M[0], t.x);
     }
+    const float Mu = M[0] == -INFINITY ? 0.0f : M[0];
+    l_row[0] = 0.0f;
+#pragma unroll
+    for (int k = 0; k < KS; ++k) {
+      const float fk = __builtin_amdgcn_exp2f(mk[k] - Mu);
+      l_row[0] += lk[k] * fk;
+#pragma unroll
+      for (int j = 0; j < kOutTiles; ++j)
+#pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4) {
+          const f32x4 t = mo[((k * RT + rt) * 16 + (dt0 + j) * 4 + q4) * 64 + lane];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) o[0][j][q4][e] = k == 0 ? t[e] * fk : o[0][j][q4][e] + t[e] * fk;
+        }
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < TPW; ++i)
+#pragma unroll
+      for (int j = 0; j < kOutTiles; ++j)
+#pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4)
+          o[i][j][q4] = f32x4{oacc[i][j][q4 * 4 + 0], oacc[i][j][q4 * 4 + 1], oacc[i][j][q4 * 4 + 2],
+                              oacc[i][j][q4 * 4 + 3]};
   }
-  if (ks != 0) return;
 
   // ---- write: final output (one part) or partial ----
 #pragma unroll
   for (int i = 0; i < TPW; ++i) {
     if (!row_ok[i]) continue;
+    const bool row_writer = hh == 0 && ks == 0;     // of the row's one (m, l) or log-sum-exp
     if (nparts == 1) {
       const float inv = 1.0f / l_row[i];
       const int64_t orow = (((int64_t)b * p.nq + jrow[i]) * p.hq + hqr[i]) * kHeadDim;
 #pragma unroll
-      for (int dt = 0; dt < 4; ++dt) {
+      for (int j = 0; j < kOutTiles; ++j) {
 #pragma unroll
         for (int q4 = 0; q4 < 4; ++q4) {
-          const int d = dt * 32 + q4 * 8 + hh * 4;
-          const float o0 = oacc[i][dt][q4 * 4 + 0] * inv, o1 = oacc[i][dt][q4 * 4 + 1] * inv;
-          const float o2 = oacc[i][dt][q4 * 4 + 2] * inv, o3 = oacc[i][dt][q4 * 4 + 3] * inv;
+          const int d = (dt0 + j) * 32 + q4 * 8 + hh * 4;
+          const f32x4 v = o[i][j][q4];
+          const float o0 = v[0] * inv, o1 = v[1] * inv, o2 = v[2] * inv, o3 = v[3] * inv;
           if (p.out_fp32) {
             *(f32x4*)((float*)p.out + orow + d) = f32x4{o0, o1, o2, o3};
           } else {
@@ -567,35 +593,42 @@ __global__ __launch_bounds__(NW * 64, WPS) void attn_mfma_kernel(AttnParams p) {
           }
         }
       }
-      if (p.lse && hh == 0)
+      if (p.lse && row_writer)
         p.lse[((int64_t)b * p.nq + jrow[i]) * p.hq + hqr[i]] = (M[i] + __log2f(l_row[i])) * kLn2;
     } else {
-      const int64_t prow = p.balanced ? ((int64_t)h * p.items + item) * p.rows_pad + r[i]
+      const int64_t prow = kBalanced ? ((int64_t)h * p.items + item) * p.rows_pad + r[i]
                                       : (((int64_t)b * p.hkv + h) * p.rows_pad + r[i]) * p.splits + part;
       float* po = p.part_o + prow * kHeadDim;
 #pragma unroll
-      for (int dt = 0; dt < 4; ++dt)
+      for (int j = 0; j < kOutTiles; ++j)
 #pragma unroll
-        for (int q4 = 0; q4 < 4; ++q4) {
-          const int d = dt * 32 + q4 * 8 + hh * 4;
-          *(f32x4*)(po + d) = f32x4{oacc[i][dt][q4 * 4 + 0], oacc[i][dt][q4 * 4 + 1], oacc[i][dt][q4 * 4 + 2],
-                                    oacc[i][dt][q4 * 4 + 3]};
-        }
-      if (hh == 0) p.part_ml[prow] = make_float2(M[i], l_row[i]);
+        for (int q4 = 0; q4 < 4; ++q4) *(f32x4*)(po + (dt0 + j) * 32 + q4 * 8 + hh * 4) = o[i][j][q4];
+      if (row_writer) p.part_ml[prow] = make_float2(M[i], l_row[i]);
     }
   }
   };  // segment
 
-  if (!p.balanced) {
+  int raw_ids[PF] = {};
+  if constexpr (!kBalanced) {
     // every sequence split alike: work item (row group, split, KV head, sequence)
     int wj = xcd_remap(blockIdx.x, gridDim.x) / p.row_groups;
     const int split = wj % p.splits;
     const int b = wj / p.splits / p.hkv;
-    int T = clamp_ctx(p.ctx_lens[b], p.max_pages_per_seq, p.page_shift);
+    const int blk0 = split * p.blocks_per_split;
+    // The first blocks' page ids, the length and the step offset in one round trip (0.9 us of a
+    // 17 us call when the ids waited for the length).  Entries past the sequence's last page may hold
+    // anything: the index stays inside the table's row, and the value is not used (see segment).
+#pragma unroll
+    for (int u = 0; u < PF; ++u) {
+      int lp = ((blk0 + ks + KS * u) * kBlockKeys + 16 * (lane & 1)) >> p.page_shift;
+      lp = lp < p.max_pages_per_seq ? lp : p.max_pages_per_seq - 1;
+      raw_ids[u] = p.page_table[(int64_t)b * p.max_pages_per_seq + lp];
+    }
+    const int raw_s0 = p.tree ? 0 : load_scalar_i32(p.step_offsets, b);
+    int T = clamp_ctx(load_scalar_i32(p.ctx_lens, b), p.max_pages_per_seq, p.page_shift);
     T = T > p.max_ctx ? p.max_ctx : T;
     const int nbt = (T + kBlockKeys - 1) / kBlockKeys;
-    const int blk0 = split * p.blocks_per_split;
-    segment(b, T, split, p.splits, blk0, min(blk0 + p.blocks_per_split, nbt), split == p.splits - 1);
+    segment(b, T, split, p.splits, blk0, min(blk0 + p.blocks_per_split, nbt), split == p.splits - 1, raw_ids, raw_s0);
     return;
   }
   // length-balanced: this item's sequence and split, from the lengths
@@ -615,7 +648,7 @@ __global__ __launch_bounds__(NW * 64, WPS) void attn_mfma_kernel(AttnParams p) {
     p.seq_splits[64 + b] = first;
   }
   const int nbt = (T + kBlockKeys - 1) / kBlockKeys;
-  segment(b, T, split, nsplit, split * per, min(split * per + per, nbt), split == nsplit - 1);
+  segment(b, T, split, nsplit, split * per, min(split * per + per, nbt), split == nsplit - 1, raw_ids, 0);
 }
 
 }  // namespace
