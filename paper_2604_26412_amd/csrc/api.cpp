@@ -92,6 +92,61 @@ int round_tiles(int rows) {
   return t <= 1 ? 1 : (t <= 2 ? 2 : (t <= 4 ? 4 : 8));
 }
 
+// Splits of the general kernel: two workgroups per CU, at least four blocks per wave.
+int generic_splits(const kvshot_ctx* c, int pairs, int nb, int key_streams) {
+  const int splits = (c->num_cus * 2 + pairs - 1) / pairs;
+  const int cap = nb / (key_streams * 4);
+  return splits > cap ? cap : splits;
+}
+
+// Splits of a call with `pairs` workgroups per split and nb key blocks: the count of least estimated time,
+// in units of one block step of a workgroup (about 1.1 us in every kernel).  A CU holds one workgroup, so
+// the grid runs in rounds of num_cus; a round costs its workgroups' steps and about 9 more for the dispatch,
+// the dependent loads of the prologue and the epilogue.  Splitting adds the merge kernel (4) and its
+// traffic.  A grid that rounds up past the chip pays a whole round for the rest, so one full round or less
+// is usual: 3 sequences of 4096 tokens with 64 rows take 38.3 us in 11 splits (264 workgroups) and 25.6 in
+// 10 (240), 9 sequences 66.9 us in 4 (288) and 42.7 in 3 (216), a 60-node tree over 3 x 8000 tokens 86.3 us
+// in 11 and 57.3 in 10.  A grid that takes (nearly) every CU also loses about a step against one that
+// leaves an eighth of them (1 x 8192 tokens: 32 splits 17.7 us, 28 splits 16.5 us; the tall kernel does
+// not).  Short contexts are split down to one step per workgroup: 1 x 1024 tokens take 17.2 us in 2
+// splits and 13.8 us in 8.
+int choose_splits(const kvshot_ctx* c, const Plan& pl, int pairs, int nb) {
+  const int target = c->num_cus * (pl.path == 1 ? mfma_wgs_per_cu(pl.kernel_row_tiles) : 1);
+  if (pl.path == 4) {
+    // float32: 16 keys and 16 rows take a wave about 1 us of matrix instructions, so one key block (two
+    // waves' work) per workgroup still gains: 512 keys, 16 rows take 21.8 us unsplit and 13.4 us in 16 splits,
+    // 4096 keys 37.7 us in 4 and 19.0 us in 32.  From 256 keys down the second launch costs a caller what the
+    // splits gain (15.9 us against 12.6 us + 3 us).  One round at most: 3 x 2048 keys 29.5 us in 11 splits (264
+    // workgroups), 19.9 us in 10.
+    const int s = target / pairs;
+    return nb <= 8 ? 1 : (s > nb ? nb : s);
+  }
+  // 256-row tiles keep four blocks per workgroup (their partials are the largest)
+  int cap = pl.kernel_row_tiles >= 8 ? nb / 4 : (nb + pl.key_streams - 1) / pl.key_streams;
+  const int widest = 2 * target / pairs;         // more than two rounds only where one split already takes them
+  cap = cap > kMaxSplits ? kMaxSplits : cap;
+  cap = cap > widest ? widest : cap;
+  int best = 1;
+  float best_cost = 0.0f;
+  for (int s = 1; s <= cap || s == 1; ++s) {
+    int bps = (nb + s - 1) / s;
+    bps = ((bps + pl.key_streams - 1) / pl.key_streams) * pl.key_streams;
+    if (s > 1 && (int64_t)bps * (s - 1) >= nb) continue;   // the same blocks per split need fewer splits
+    const int64_t wgs = (int64_t)pairs * s;
+    const int rounds = (int)((wgs + target - 1) / target);
+    // two rounds only while the partials of 128 rows fit the no-allocation call's scratch
+    if (s > 1 && rounds > 1 && wgs * pl.rows_pad > 60000) continue;
+    float cost = rounds * (9.0f + (float)(bps / pl.key_streams));
+    if (pl.path != 3 && rounds == 1 && wgs * 8 > (int64_t)target * 7) cost += 1.0f;
+    if (s > 1) cost += 4.0f + (float)wgs * pl.rows / 6340.0f;
+    if (s == 1 || cost < best_cost) {
+      best = s;
+      best_cost = cost;
+    }
+  }
+  return best;
+}
+
 Plan make_plan(const kvshot_ctx* c, int batch, int nq, int max_ctx, bool allow_tall = true) {
   Plan pl{};
   pl.rows = c->group * nq;
@@ -128,20 +183,7 @@ Plan make_plan(const kvshot_ctx* c, int batch, int nq, int max_ctx, bool allow_t
   if (c->opt_splits > 0) {
     splits = c->opt_splits;
   } else {
-    // One round of resident workgroups over the chip: split the context only
-    // when the (sequence, KV head) pairs alone leave CUs idle, and keep >= 4
-    // blocks per wave.  (Each workgroup starts with a dependent chain of
-    // loads -- length, page ids, K/V, RoPE table -- that only other resident
-    // workgroups can hide, so more, shorter workgroups lose.)
-    const int per_cu = pl.path == 2 ? 2 : (pl.path == 3 || pl.path == 4 ? 1 : mfma_wgs_per_cu(pl.kernel_row_tiles));
-    const int target_wgs = c->num_cus * per_cu;
-    splits = (target_wgs + pairs - 1) / pairs;
-    // float32: 16 keys and 16 rows take a wave about 1 us of matrix instructions, so one key block
-    // (two waves' work) per workgroup still gains: 512 keys, 16 rows take 21.8 us unsplit and 13.4 us
-    // in 16 splits, 4096 keys 37.7 us in 4 and 19.0 us in 32.  From 256 keys down the second launch
-    // costs a caller what the splits gain (15.9 us against 12.6 us + 3 us).
-    const int cap = pl.path == 4 ? (nb > 8 ? nb : 1) : nb / (pl.key_streams * 4);
-    splits = splits > cap ? cap : splits;
+    splits = pl.path == 2 ? generic_splits(c, pairs, nb, pl.key_streams) : choose_splits(c, pl, pairs, nb);
   }
   if (splits < 1) splits = 1;
   // the tall-tile kernel stages a split's page ids in LDS: at most tall_max_blocks() blocks per split

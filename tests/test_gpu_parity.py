@@ -276,6 +276,23 @@ def test_ragged_tails_and_empty_prefix(lens):
     _check_case(c, what=f"tails {lens}")
 
 
+@pytest.mark.parametrize("batch,n", [(1, 3), (1, 16), (3, 16), (9, 12), (5, 30), (3, 60), (40, 2)])
+def test_automatic_splits_of_odd_batches(batch, n):
+    """Split counts that the estimated time chooses where a batch does not divide the chip: one round of
+    workgroups or two full ones, down to one block step per workgroup (waves of the last split without a
+    block among them), every row-tile height; partials of up to 128 rows fit the no-allocation scratch."""
+    lens = [700 - 61 * (b % 11) for b in range(batch)]
+    c = small(batch=batch, ctx_lens=lens, n_new=n, max_draft=n, seed=41 + batch + n)
+    with G.handle_for(c) as att:
+        pl = att.plan(batch, n, 700)
+        cus = G.torch().cuda.get_device_properties(0).multi_processor_count
+        pairs = batch * c.num_kv_heads
+        if pl["workgroups"] == pl["splits"] * pairs:      # not the length-balanced plan
+            assert pl["splits"] == 1 or pl["workgroups"] <= 2 * cus, pl
+            assert pl["splits"] == 1 or pl["row_tiles"] > 4 or pairs * pl["splits"] * 32 * pl["row_tiles"] * 520 < 32 << 20
+    _check_case(c, what=f"odd batch {batch}, {n} steps, plan {pl}")
+
+
 _BALANCED_LENS = [
     # 32 sequences (the largest batch the balanced plan takes with 8 KV heads on 256 CUs): one long
     # prefix among empty, sub-block, block-edge and page-edge lengths
