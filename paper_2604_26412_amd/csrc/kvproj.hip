@@ -19,11 +19,16 @@
 //
 // Operand movement: both tiles go straight from global memory into LDS with
 // global_load_lds_dwordx4 (no register staging, no LDS store instructions),
-// NS stages deep: NS - 1 chunks are in flight while one is computed, one
-// barrier per chunk.  Each load is a wave-wide 1 KB block of LDS, so the rows
-// are unpadded and an XOR swizzle on the load side keeps the fragment reads
-// free of bank conflicts.  A chunk's loads are issued one per four MFMAs of
-// the chunk before it.
+// into two stages of one 64-wide chunk each, one barrier per chunk.  Each load
+// is a wave-wide 1 KB block of LDS, so the rows are unpadded and an XOR swizzle
+// on the load side keeps the fragment reads free of bank conflicts.  A row of a
+// chunk is 128 bytes, a whole cache line: with 32-wide chunks in four stages
+// every line was read in two halves, a chunk apart, and the loads bound the
+// loop (262,144 tokens, 8 KV heads: 3154 us then, 2975 us now, 1.11 PFLOP/s).
+// Timing copies of this loop put what is left at 2385 us without any loads and
+// 2680 us with every load a hit in L2; spreading the loads over more of the
+// chunk, touching lines two chunks ahead, eight waves instead of four, and
+// fewer channel tiles per XCD were no faster.
 //
 // Epilogue: RoPE on keys in registers (angles reduced in float64, sine and
 // cosine from the hardware units), bf16 rounding, and 8-byte stores into the
@@ -52,12 +57,7 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
-#ifndef KVSHOT_KVPROJ_KC
-#define KVSHOT_KVPROJ_KC 32
-#endif
-#ifndef KVSHOT_KVPROJ_NS
-#define KVSHOT_KVPROJ_NS 4
-#endif
+constexpr int KC = 64;    // reduction indices per chunk (two LDS stages of them)
 typedef __attribute__((address_space(3))) void lds_void;
 
 __device__ __forceinline__ bf16x8 as_bf16x8(u32x4 v) { return __builtin_bit_cast(bf16x8, v); }
@@ -91,31 +91,23 @@ __device__ __forceinline__ void load_to_lds16(const void* src, const void* lds) 
 }
 #pragma clang diagnostic pop
 
-// Row swizzle of the LDS operand tiles (rows of KC bf16 = KC / 8 pieces of 16 bytes): piece q
-// of row r is stored in slot q ^ swizzle(r).  Chosen so that 8 or 16 consecutive rows read at
-// one logical piece cover distinct 4-byte bank groups with 32 or 64 banks, and so that it
-// depends on bits 0..4 of r only (a fragment row is 32 i + lane % 32 above a multiple of 32).
-template <int KC>
-__device__ __forceinline__ int swizzle(int r) {
-  if constexpr (KC == 64) return (r ^ ((r >> 3) & 3)) & 7;
-  else if constexpr (KC == 32) return ((r >> 1) ^ (r >> 2)) & 3;
-  else return ((r >> 2) ^ (r >> 3)) & 1;
-}
+// Row swizzle of the LDS operand tiles (rows of KC bf16 = 8 pieces of 16 bytes): piece q of row r
+// is stored in slot q ^ swizzle(r).  Chosen so that 8 or 16 consecutive rows read at one logical
+// piece cover distinct 4-byte bank groups with 32 or 64 banks, and so that it depends on bits 0..4
+// of r only (a fragment row is 32 i + lane % 32 above a multiple of 32).
+__device__ __forceinline__ int swizzle(int r) { return (r ^ ((r >> 3) & 3)) & 7; }
 
-// KC: reduction indices per chunk; NS: LDS stages (chunks in flight: NS - 1).
-template <bool SPLIT, int KC, int NS>
+template <bool SPLIT>
 __global__ __launch_bounds__(256, 1) void kvproj_kernel(KvProjParams p) {
   constexpr int kPieces = KC / 8;                   // 16-byte pieces per operand row and chunk
   constexpr int kRowsPerLoad = 64 / kPieces;        // operand rows one wave-wide 16-byte load covers
   constexpr int kLoads = kProjTile / kRowsPerLoad / 4;   // loads per wave, operand and chunk
   constexpr int kStageElems = kProjTile * KC;       // one operand tile (bf16)
   constexpr int kSteps = KC / 16;                   // MFMA k-steps per chunk
-  static_assert(KC == 16 || KC == 32 || KC == 64, "chunk");
-  static_assert(NS >= 2 && NS * 2 * kStageElems * 2 <= 136 * 1024, "stages fit in LDS");
   // Operand rows are KC * 2 bytes with no padding.  Piece q of row r sits at physical slot
   // q ^ swz(r) (see swizzle()): the lanes one LDS cycle serves -- 8 or 16 consecutive rows at
   // one logical piece -- then hit distinct bank groups.
-  __shared__ __attribute__((aligned(16))) uint16_t smem[NS * 2 * kStageElems];
+  __shared__ __attribute__((aligned(16))) uint16_t smem[2 * 2 * kStageElems];
   __shared__ int64_t t_src[kProjTile];   // source element offset of each token's slot (page, slot)
   __shared__ int64_t t_dst[kProjTile];   // destination element offset
   __shared__ int32_t t_pos[kProjTile];   // position, clamped to the RoPE table
@@ -175,13 +167,14 @@ __global__ __launch_bounds__(256, 1) void kvproj_kernel(KvProjParams p) {
 #pragma unroll
   for (int j = 0; j < kLoads; ++j) {
     const int r = kRowsPerLoad * (kLoads * w + j) + lane / kPieces;
-    const int q = (lane % kPieces) ^ swizzle<KC>(r);
+    const int q = (lane % kPieces) ^ swizzle(r);
     soff[j] = t_src[r] + 8 * q;
     const int wrow = mt * kProjTile + r;
     woff[j] = (wrow < d_kv ? wrow : d_kv - 1) * K + 8 * q;
   }
   const uint16_t* wsrc = g ? p.w_v : p.w_k;
-  const int nch = (cend - cbeg) * (64 / KC);      // chunks of this split (the split plan counts 64-wide ones)
+  static_assert(KC == 64, "the split plan counts 64-wide chunks");
+  const int nch = cend - cbeg;                    // chunks of this split
   const int k_first = cbeg * 64;
   // the 2 kLoads loads of chunk c into `stage`: the first kLoads are weight rows, the rest token rows
   struct Target {
@@ -229,12 +222,10 @@ __global__ __launch_bounds__(256, 1) void kvproj_kernel(KvProjParams p) {
 
   // fragment reads: row R = (wave base) + 32 i + lane % 32 has swizzle(R) == swizzle(lane % 32); lane half hh
   // covers logical pieces hh kSteps .. hh kSteps + kSteps - 1, k-step s takes piece hh kSteps + s
-  const int swz = swizzle<KC>(lane & 31);
+  const int swz = swizzle(lane & 31);
   int frag_off[kSteps];
 #pragma unroll
   for (int st = 0; st < kSteps; ++st) frag_off[st] = 8 * ((hh * kSteps + st) ^ swz);
-  static_assert(2 * kLoads == 4 * kSteps, "one load per four MFMAs");
-  static_assert(NS >= 3, "the next chunk is read while a later one is still in flight");
   // Fragments of one k-step, double-buffered across k-steps and across chunks.
   bf16x8 a[2][4], b[2][4];
   auto read = [&](int stage, int st, bf16x8 (&fa)[4], bf16x8 (&fb)[4]) {
@@ -245,59 +236,56 @@ __global__ __launch_bounds__(256, 1) void kvproj_kernel(KvProjParams p) {
 #pragma unroll
     for (int j = 0; j < 4; ++j) fb[j] = as_bf16x8(*(const u32x4*)(B + 32 * j * KC + frag_off[st]));
   };
-  // Chunk c from `stage` (its first k-step's fragments already read), with the loads of a later
-  // chunk (`nt`) issued one per four MFMAs (so no wave stalls on a burst of load issues before its
-  // first MFMA) and the next k-step's fragments read during the current one -- in the last k-step,
-  // those of chunk c + 1's first k-step from `next_stage`.  The chunk's one barrier sits before
-  // its last k-step: by then every wave has its share of chunk c + 1 in LDS (the wait before the
-  // barrier) and has finished reading chunk c - 1, whose stage the loads refill; so the first
-  // reads of the next chunk no longer wait behind a barrier with nothing to compute.  The order is
-  // pinned with scheduling barriers.
-  auto compute = [&](int stage, int next_stage, const Target& nt) {
-#pragma unroll
-    for (int st = 0; st < kSteps; ++st) {
-      if (st + 1 == kSteps) {
-        // in flight may stay: the NS - 3 chunks after c + 1 and this chunk's loads so far
-        wait_vmcnt<(NS - 3) * 2 * kLoads + 4 * (kSteps - 1)>();
-        lds_barrier();
-        __builtin_amdgcn_sched_barrier(0);
-      }
-      if (st + 1 < kSteps) read(stage, st + 1, a[(st + 1) & 1], b[(st + 1) & 1]);
-      else read(next_stage, 0, a[(st + 1) & 1], b[(st + 1) & 1]);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[st & 1][i], b[st & 1][j], acc[i][j], 0, 0, 0);
-        __builtin_amdgcn_sched_barrier(0);
-        issue_one(nt, 4 * st + i);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    }
-  };
   static_assert(kSteps % 2 == 0, "a chunk's first k-step uses fragment buffer 0");
+  static_assert(kLoads == 8, "half of a chunk's loads go out in one k-step, one per two MFMAs");
 
-  // ---- main loop.  Chunks 0 .. NS - 2 are issued up front, chunk 0 is waited for and its first
-  // k-step read; iteration c computes c from stage c % NS while issuing chunk c + NS - 1 into the
-  // stage of chunk c - 1 (free: every wave finished reading it before chunk c - 1's barrier).
-  // Loads past the last chunk re-read it into a stage nobody reads again, and the last chunk's
-  // reads of "the next chunk" read a stage whose values are never used. ----
+  // ---- main loop.  Chunk c is computed from stage c % 2, its first k-step's fragments already read.
+  // Each k-step reads the next one's fragments, the last one those of chunk c + 1's first k-step from
+  // the other stage.  The chunk's one barrier sits before its last k-step: by then every wave has
+  // its share of chunk c + 1 in LDS (the wait before the barrier) and the fragments of its last
+  // k-step in registers, so that the stage is free, and the loads of chunk c + 2 into it are issued
+  // over that k-step and the first one of chunk c + 1, one per two MFMAs, token rows first (they
+  // come from further away); two k-steps are left for the last of them to land.  The order is pinned
+  // with scheduling barriers.  Loads past the last chunk re-read it into a stage nobody reads again,
+  // and the last chunk's reads of "the next chunk" read a stage whose values are never used. ----
+  auto issue = [&](const Target& t, int k) { issue_one(t, k < kLoads ? kLoads + k : k - kLoads); };
+  Target next = target(0);
 #pragma unroll
-  for (int c = 0; c < NS - 1; ++c) {
-    const Target t = target(c);
+  for (int k = 0; k < 2 * kLoads; ++k) issue(next, k);
+  advance();
+  next = target(1);
 #pragma unroll
-    for (int idx = 0; idx < 2 * kLoads; ++idx) issue_one(t, idx);
-    advance();
-  }
-  wait_vmcnt<(NS - 2) * 2 * kLoads>();
+  for (int k = 0; k < kLoads; ++k) issue(next, k);
+  wait_vmcnt<kLoads>();
   lds_barrier();
   read(0, 0, a[0], b[0]);
   int stage = 0;
   for (int c = 0; c < nch; ++c) {
-    const int next_stage = stage == NS - 1 ? 0 : stage + 1;
-    compute(stage, next_stage, target(stage == 0 ? NS - 1 : stage - 1));   // the cursor is at chunk c + NS - 1 (clamped)
-    advance();
-    stage = next_stage;
+#pragma unroll
+    for (int st = 0; st < kSteps; ++st) {
+      if (st + 1 == kSteps) {
+        wait_vmcnt<0>();
+        lds_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+        advance();
+        next = target(stage);
+      }
+      if (st + 1 < kSteps) read(stage, st + 1, a[(st + 1) & 1], b[(st + 1) & 1]);
+      else read(stage ^ 1, 0, a[(st + 1) & 1], b[(st + 1) & 1]);
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[st & 1][i], b[st & 1][j], acc[i][j], 0, 0, 0);
+          if (j & 1) {
+            __builtin_amdgcn_sched_barrier(0);
+            if (st + 1 == kSteps) issue(next, 2 * i + (j >> 1));
+            if (st == 0) issue(next, kLoads + 2 * i + (j >> 1));
+            __builtin_amdgcn_sched_barrier(0);
+          }
+        }
+    }
+    stage ^= 1;
   }
   wait_vmcnt<0>();     // the trailing re-reads land before the workgroup ends
 
@@ -681,11 +669,10 @@ __global__ void fill_kernel(int32_t* flag, int32_t v) { *flag = v; }
 
 hipError_t launch_kvproj(const KvProjParams& p, hipStream_t s) {
   const int grid = (p.work_items + 7) / 8 * 8;
-  constexpr int KC = KVSHOT_KVPROJ_KC, NS = KVSHOT_KVPROJ_NS;
   if (p.splits > 1)
-    hipLaunchKernelGGL((kvproj_kernel<true, KC, NS>), dim3(grid), dim3(256), 0, s, p);
+    hipLaunchKernelGGL(kvproj_kernel<true>, dim3(grid), dim3(256), 0, s, p);
   else
-    hipLaunchKernelGGL((kvproj_kernel<false, KC, NS>), dim3(grid), dim3(256), 0, s, p);
+    hipLaunchKernelGGL(kvproj_kernel<false>, dim3(grid), dim3(256), 0, s, p);
   return hipGetLastError();
 }
 

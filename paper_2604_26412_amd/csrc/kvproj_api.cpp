@@ -73,7 +73,7 @@ int plan_splits(const kvshot_kvproj_ctx* c, int n_tokens) {
 // (64 + 16 tile16) rows of the reduction.  The automatic choice compares two
 // estimates fitted to MI355X timings (Hkv 4 to 16, 64 to 16384 tokens): a
 // direct round costs about 4 us plus its operand rows at 60 GB/s per CU (one
-// workgroup per CU), a tiled round 6 us plus 512 rows at 32 GB/s per CU, and
+// workgroup per CU), a tiled round 10 us plus 512 rows at 60 GB/s per CU, and
 // split partials are written and read back at about 5 TB/s plus 2 us.
 struct ProjPlan {
   int path = 1, splits = 1, tile16 = 0, tiles = 0, workgroups = 0;
@@ -109,7 +109,7 @@ ProjPlan tiled_plan(const kvshot_kvproj_ctx* c, int n_tokens, double* est_us) {
   pl.workgroups = 2 * m_tiles_of(c) * pl.tiles * pl.splits;
   const double row_bytes = 2.0 * c->cfg.num_layers * c->cfg.num_kv_heads * kHeadDim / pl.splits;
   const int64_t rounds = (pl.workgroups + c->num_cus - 1) / c->num_cus;
-  double us = (double)rounds * (6.0 + 512 * row_bytes / 32e3);
+  double us = (double)rounds * (10.0 + 512 * row_bytes / 60e3);
   if (pl.splits > 1)
     us += 2.0 + 2.0 * pl.splits * (double)n_tokens * 2 * c->cfg.num_kv_heads * kHeadDim * 4 / 5e6;
   *est_us = us;
