@@ -204,18 +204,18 @@ Plan make_plan(const kvshot_ctx* c, int batch, int nq, int max_ctx, bool allow_t
   // them over the chip (four per CU), shared out as work items per KV head over the sequences in
   // proportion to their lengths (computed on the device from ctx_lens), instead of giving every
   // sequence the same split count.  With four times the items of four-wave workgroups, a sequence's
-  // whole-number share of them is four times finer.  Below three eighths as many sequences as items (47
+  // whole-number share of them is four times finer.  Up to a third as many sequences as items (42
   // with 8 KV heads) where the prompts reach 2048 tokens, a quarter below: one workgroup per (sequence,
   // KV head) leaves much of the chip idle in its second round there, or waits for the longest
   // prompt (36 sequences of 4096 tokens 129.7 us unsplit, 112.8 balanced, of 1000 to 16000 tokens 289.5
   // and 206.9; of 300 to 800 tokens 30.7 and 34.1).  Larger batches fill the chip, and their unsplit plan
-  // needs no partials and no combine (52 x 4096: 141.9 and 158.1 us, 64 x 4096: 170.0 and 180.6; 64 x 32K:
+  // needs no partials and no combine (46 x 4600 with 8 steps: 159 and 170 us, 52 x 4096: 141.9 and 158.1, 64 x 4096: 170.0 and 180.6; 64 x 32K:
   // the balanced plan's combine adds 16 us to a 1.26 ms step).
   if (pl.path == 1 && pl.kernel_row_tiles == 1 && c->opt_splits == 0 && batch >= 2 && batch <= 64) {
     const int per_cu = mfma_wgs_per_cu(1) * mfma_waves_per_wg(1);   // one-wave workgroups per CU
     int items = c->num_cus * per_cu / c->cfg.num_kv_heads;
     while (items > 1 && (size_t)c->cfg.num_kv_heads * pl.rows_pad * items > c->ws_rows) --items;
-    if (4 * batch <= items || (nb >= 64 && 8 * batch < 3 * items)) {
+    if (4 * batch <= items || (nb >= 64 && 3 * batch <= items)) {
       pl.balanced = 1;
       pl.items = items;
       pl.min_chunk = 1;

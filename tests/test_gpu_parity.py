@@ -297,8 +297,8 @@ _BALANCED_LENS = [
     # 32 sequences (the largest batch of short prompts the balanced plan takes with 8 KV heads on 256 CUs): one long
     # prefix among empty, sub-block, block-edge and page-edge lengths
     [9000] + [0, 1, 31, 32, 33, 64, 65, 100, 511, 512, 513] * 2 + [7, 3, 2000, 4096, 0, 1, 15, 16, 17],
-    # 47 sequences, the largest batch with prompts of 2048 tokens and more
-    [2100, 2048, 0, 1, 700, 33] * 7 + [2100, 31, 32, 2049, 5],
+    # 42 sequences, the largest batch with prompts of 2048 tokens and more
+    [2100, 2048, 0, 1, 700, 33] * 6 + [2100, 31, 32, 2049, 5, 16],
     # one prefix long enough that its share of the items hits the per-sequence cap of 64 splits
     [40000, 16],
     # every prefix shorter than one block (the handle sized for 1024-token prefixes, so that its
@@ -307,7 +307,7 @@ _BALANCED_LENS = [
 ]
 
 
-@pytest.mark.parametrize("lens", _BALANCED_LENS, ids=["b32_mixed", "b47_long", "b2_capped", "b16_tiny"])
+@pytest.mark.parametrize("lens", _BALANCED_LENS, ids=["b32_mixed", "b42_long", "b2_capped", "b16_tiny"])
 def test_balanced_schedule_extremes(lens):
     """Length-balanced split schedule (computed on the device from the lengths): every sequence's
     items, the per-sequence split cap, empty and sub-block prefixes, checked against the oracle."""
