@@ -55,8 +55,9 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// TB: 16-token blocks; CB: 16-channel blocks; CROSS: n is zero and its segment is skipped.
-template <int TB, int CB, int NW, int PFA, int PFW, bool PACKED, bool CROSS>
+// TB: 16-token blocks; CB: 16-channel blocks; CROSS: n is zero and its segment is skipped; NT: the weights are
+// read with the non-temporal hint.
+template <int TB, int CB, int NW, int PFA, int PFW, bool PACKED, bool CROSS, bool NT>
 __global__ __launch_bounds__(NW * 64, NW / 4) void fusion_slim_kernel(FusionParams p) {
   static_assert(PFW % PFA == 0, "the loop is unrolled over the weight ring");
   constexpr int TT = 16 * TB;
@@ -118,7 +119,9 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void fusion_slim_kernel(FusionPara
         for (int cb = 0; cb < CB; ++cb) {
           const int64_t at = PACKED ? (int64_t)c * 8192 + (ok ? i * 256 + cb * cstride : 0)
                                     : c * kChunk + (ok ? i * 32 + cb * (kSegOf[s] < 3 ? 3 : 1) * cstride : 0);
-          dst[s][i][cb] = *(const u32x4*)(wbase[ok ? s : 0] + at);
+          const u32x4* src = (const u32x4*)(wbase[ok ? s : 0] + at);
+          if constexpr (NT) dst[s][i][cb] = __builtin_nontemporal_load(src);
+          else dst[s][i][cb] = *src;
         }
   };
   auto load_a = [&](int it, u32x4 (&dst)[kTensors][kRowLoads]) {
@@ -240,11 +243,13 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void fusion_slim_kernel(FusionPara
   }
 }
 
-template <int TB, int CB, int NW, int PFA, int PFW, bool PACKED>
+template <int TB, int CB, int NW, int PFA, int PFW, bool PACKED, bool NT>
 void launch_slim_t(const FusionParams& p, hipStream_t s) {
   const dim3 grid((unsigned)(p.d / (16 * CB))), block(NW * 64);
-  if (p.cross_only) hipLaunchKernelGGL((fusion_slim_kernel<TB, CB, NW, PFA, PFW, PACKED, true>), grid, block, 0, s, p);
-  else hipLaunchKernelGGL((fusion_slim_kernel<TB, CB, NW, PFA, PFW, PACKED, false>), grid, block, 0, s, p);
+  if (p.cross_only)
+    hipLaunchKernelGGL((fusion_slim_kernel<TB, CB, NW, PFA, PFW, PACKED, true, NT>), grid, block, 0, s, p);
+  else
+    hipLaunchKernelGGL((fusion_slim_kernel<TB, CB, NW, PFA, PFW, PACKED, false, NT>), grid, block, 0, s, p);
 }
 
 // Waves and ring depths by token blocks and channels, the fastest of those measured (us at d = 4096, or
@@ -256,25 +261,33 @@ void launch_slim_t(const FusionParams& p, hipStream_t s) {
 //   16 x 32  8 waves 2,2: 31.3; 4 waves 2,2: 30.6 (row-major weights 43.3 and 51.2)
 //   32 x 32  4 waves 2,2: 34.6; 4,4: 35.3; 8 waves 1,2: 34.5 (row-major 46.6, 47.3, 50.8)
 //   64 x 32  4 waves 1,1: 37.7; 1,2: 41.1 (row-major weights 61.8 and 55.0)
-template <bool PACKED>
+template <bool PACKED, bool NT>
 void launch_slim(const FusionParams& p, hipStream_t s) {
   if (p.tile_channels == 16) {
-    if (p.tokens <= 16) launch_slim_t<1, 1, 8, 1, 2, PACKED>(p, s);
-    else if (p.tokens <= 32) launch_slim_t<2, 1, 8, 1, 1, PACKED>(p, s);
-    else if (p.tokens <= 64) launch_slim_t<4, 1, 4, 2, 2, PACKED>(p, s);
-    else launch_slim_t<6, 1, 4, 1, 1, PACKED>(p, s);
+    if (p.tokens <= 16) launch_slim_t<1, 1, 8, 1, 2, PACKED, NT>(p, s);
+    else if (p.tokens <= 32) launch_slim_t<2, 1, 8, 1, 1, PACKED, NT>(p, s);
+    else if (p.tokens <= 64) launch_slim_t<4, 1, 4, 2, 2, PACKED, NT>(p, s);
+    else launch_slim_t<6, 1, 4, 1, 1, PACKED, NT>(p, s);
   } else {
-    if (p.tokens <= 16) launch_slim_t<1, 2, 8, 2, 2, PACKED>(p, s);
-    else if (p.tokens <= 32) launch_slim_t<2, 2, 4, 2, 2, PACKED>(p, s);
-    else launch_slim_t<4, 2, 4, 1, PACKED ? 1 : 2, PACKED>(p, s);
+    if (p.tokens <= 16) launch_slim_t<1, 2, 8, 2, 2, PACKED, NT>(p, s);
+    else if (p.tokens <= 32) launch_slim_t<2, 2, 4, 2, 2, PACKED, NT>(p, s);
+    else launch_slim_t<4, 2, 4, 1, PACKED ? 1 : 2, PACKED, NT>(p, s);
   }
 }
 
 }  // namespace
 
 hipError_t launch_fusion_slim(const FusionParams& p, hipStream_t s) {
-  if (p.w_packed) launch_slim<true>(p, s);
-  else launch_slim<false>(p, s);
+  // Packed weights of more than 100 MiB (d > 3584) do not stay in the 256 MB last-level cache from one call
+  // to the next beside what else a draft step reads, and stream faster with the non-temporal hint; smaller
+  // ones do stay, and the hint gives that up.  With other weights between the calls, plain and hinted: d =
+  // 4096 1 token 24.3 and 21.6 us, 16 tokens 25.1 and 22.9, 64 tokens 33.7 and 31.9, d = 5120 8 tokens 38.1
+  // and 36.4; d = 3584 28.3 and 28.3, d = 3072 19.2 and 24.5 (64 tokens).  Row-major loads take 64 bytes of
+  // a line at a time and need the cache.
+  const bool large = (int64_t)8 * p.d * p.d > (100 << 20);
+  if (p.w_packed && large) launch_slim<true, true>(p, s);
+  else if (p.w_packed) launch_slim<true, false>(p, s);
+  else launch_slim<false, false>(p, s);
   return hipGetLastError();
 }
 
