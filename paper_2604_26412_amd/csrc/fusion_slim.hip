@@ -257,6 +257,7 @@ void launch_slim_t(const FusionParams& p, hipStream_t s) {
 //   16 x 16  8 waves 1,2: 21.0; 2,2: 21.1; 3,3: 21.8; 4,4: 21.9; 4 waves 4,4: 21.7
 //   32 x 16  8 waves 1,1: 22.9; 1,2: 23.5; 2,2: 24.2; 4 waves 4,4: 24.2
 //   64 x 16  4 waves 2,2: 26.6; 3,3: 28.0; 2,4: 28.1; 8 waves 1,2: 28.3
+//            (other weights in between, non-temporal: 31.7; 33.3; 33.5; 32.5)
 //   96 x 16  4 waves 1,1: 36.1; 1,2: 36.2; 2,2: 41.4
 //   16 x 32  8 waves 2,2: 31.3; 4 waves 2,2: 30.6 (row-major weights 43.3 and 51.2)
 //   32 x 32  4 waves 2,2: 34.6; 4,4: 35.3; 8 waves 1,2: 34.5 (row-major 46.6, 47.3, 50.8)
